@@ -208,150 +208,161 @@ __device__ __forceinline__ void copy_body(V *__restrict__ d, const V *__restrict
                                           uint64_t lane, uint64_t nl)
 {
     uint64_t i = lane;
-    if constexpr (U > 1) {
-        for (; i + (uint64_t)(U - 1) * nl < nv; i += (uint64_t)U * nl) {
-            V r[U];
+    for (; i + (uint64_t)(U - 1) * nl < nv; i += (uint64_t)U * nl) {
+        V r[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) r[u] = ld<NT>(s + i + (uint64_t)u * nl);
+        for (int u = 0; u < U; ++u) r[u] = ld<NT>(s + i + (uint64_t)u * nl);
 #pragma unroll
-            for (int u = 0; u < U; ++u) st<NT>(d + i + (uint64_t)u * nl, r[u]);
-        }
+        for (int u = 0; u < U; ++u) st<NT>(d + i + (uint64_t)u * nl, r[u]);
     }
     for (; i < nv; i += nl) st<NT>(d + i, ld<NT>(s + i));
 }
 
-/* The n < A bytes before or after the vector body of a copy by one lane
- * whose source and destination agree modulo A, in the widest naturally
- * aligned pieces: an 8-byte message is one 8-byte move, not eight. */
-template <uint64_t A>
-__device__ __forceinline__ void copy_edge_lone(uint8_t *d, const uint8_t *s, uint64_t n)
-{
-    for (uint64_t o = 0; o < n;) {
-        const uint64_t a = (uintptr_t)(d + o), r = n - o;
-        if (A > 8 && (a & 7) == 0 && r >= 8) {
-            *(uint64_t *)(d + o) = *(const uint64_t *)(s + o);
-            o += 8;
-        } else if (A > 4 && (a & 3) == 0 && r >= 4) {
-            *(uint32_t *)(d + o) = *(const uint32_t *)(s + o);
-            o += 4;
-        } else if (A > 2 && (a & 1) == 0 && r >= 2) {
-            *(uint16_t *)(d + o) = *(const uint16_t *)(s + o);
-            o += 2;
-        } else {
-            d[o] = s[o];
-            o += 1;
-        }
-    }
-}
-
-/* Copy n bytes whose source and destination agree modulo sizeof(V): byte
- * edges, then the vector body.  Cooperating lanes take one edge byte each
- * (one instruction); a lone lane (LONE: the caller passes lane 0 of 1)
- * takes wide pieces.  LONE is a template parameter rather than a test of
- * nl so that the cooperative copies compile exactly as without it. */
-template <typename V, int U, bool NT, bool LONE = false>
+/* Copy n bytes in the widest elements (16, 8, 4 bytes) on whose size source
+ * and destination agree, else in bytes, with byte edges. */
+template <typename V, int U, bool NT>
 __device__ __forceinline__ void copy_aligned(uint8_t *__restrict__ d, const uint8_t *__restrict__ s,
                                              uint64_t n, uint64_t lane, uint64_t nl)
 {
     constexpr uint64_t A = sizeof(V);
     uint64_t head = (A - ((uintptr_t)d & (A - 1))) & (A - 1);
     if (head > n) head = n;
-    if constexpr (LONE) copy_edge_lone<A>(d, s, head);
-    else
-        for (uint64_t i = lane; i < head; i += nl) d[i] = s[i];
+    for (uint64_t i = lane; i < head; i += nl) d[i] = s[i];
     uint64_t nv = (n - head) / A;
     copy_body<V, U, NT>((V *)(d + head), (const V *)(s + head), nv, lane, nl);
-    if constexpr (LONE) {
-        const uint64_t t = head + nv * A;
-        copy_edge_lone<A>(d + t, s + t, n - t);
-    } else {
-        for (uint64_t i = head + nv * A + lane; i < n; i += nl) d[i] = s[i];
-    }
-}
-
-/* Body of a copy whose source is `sh` = 4*Q + r bytes (1 <= sh <= 15) past
- * a 16-byte boundary while the destination is 16-byte aligned: destination
- * vector i is bytes [16i + sh, 16i + sh + 16) of the aligned source stream
- * s_al, taken from the two aligned vectors that hold them with byte funnel
- * shifts (v_alignbyte_b32).  Both loaded vectors hold bytes of the source
- * range, so no load touches a page the range does not touch.  Neighbouring
- * lanes load each other's vectors, which the caches absorb: HBM still
- * reads each source byte once. */
-template <int Q, int U, bool NT>
-__device__ __forceinline__ void copy_shifted_body(v4u *__restrict__ d, const v4u *__restrict__ s_al, uint32_t r,
-                                                  uint64_t nv, uint64_t lane, uint64_t nl)
-{
-    auto join = [r](const v4u &a, const v4u &b) {
-        const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        v4u o;
-        o.x = __builtin_amdgcn_alignbyte(w[Q + 1], w[Q + 0], r);
-        o.y = __builtin_amdgcn_alignbyte(w[Q + 2], w[Q + 1], r);
-        o.z = __builtin_amdgcn_alignbyte(w[Q + 3], w[Q + 2], r);
-        o.w = __builtin_amdgcn_alignbyte(w[Q + 4], w[Q + 3], r);
-        return o;
-    };
-    uint64_t i = lane;
-    for (; i + (uint64_t)(U - 1) * nl < nv; i += (uint64_t)U * nl) {
-        v4u a[U], b[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            a[u] = ld<NT>(s_al + i + (uint64_t)u * nl);
-            b[u] = ld<NT>(s_al + i + (uint64_t)u * nl + 1);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) st<NT>(d + i + (uint64_t)u * nl, join(a[u], b[u]));
-    }
-    for (; i < nv; i += nl) st<NT>(d + i, join(ld<NT>(s_al + i), ld<NT>(s_al + i + 1)));
+    for (uint64_t i = head + nv * A + lane; i < n; i += nl) d[i] = s[i];
 }
 
 template <int U, bool NT>
-__device__ __forceinline__ void copy_shifted(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n,
-                                             uint64_t lane, uint64_t nl)
-{
-    uint64_t head = (16 - ((uintptr_t)d & 15)) & 15;
-    if (head > n) head = n;
-    for (uint64_t i = lane; i < head; i += nl) d[i] = s[i];
-    const uint8_t *sb = s + head;
-    const uint64_t nv = (n - head) / 16;
-    const uint32_t sh = (uint32_t)((uintptr_t)sb & 15);   // not 0: source and destination disagree mod 16
-    const v4u *s_al = (const v4u *)(sb - sh);
-    v4u *db = (v4u *)(d + head);
-    // Two loads per stored vector: half the unroll keeps the same bytes in
-    // flight without raising register pressure in the aligned path's kernels.
-    constexpr int US = U > 2 ? U / 2 : 1;
-    switch (sh >> 2) {
-    case 0: copy_shifted_body<0, US, NT>(db, s_al, sh & 3, nv, lane, nl); break;
-    case 1: copy_shifted_body<1, US, NT>(db, s_al, sh & 3, nv, lane, nl); break;
-    case 2: copy_shifted_body<2, US, NT>(db, s_al, sh & 3, nv, lane, nl); break;
-    default: copy_shifted_body<3, US, NT>(db, s_al, sh & 3, nv, lane, nl); break;
-    }
-    for (uint64_t i = head + nv * 16 + lane; i < n; i += nl) d[i] = s[i];
-}
-
-/* Copies shorter than this take the narrower vector paths below when source
- * and destination disagree modulo 16. */
-constexpr uint64_t kShiftedMin = 256;
-
-/* Copy n bytes with nl cooperating lanes (this one is `lane`): 16-byte
- * vectors when source and destination agree modulo 16; otherwise, with
- * SHIFT, 16-byte destination vectors assembled from the source by funnel
- * shifts (copies of kShiftedMin bytes or more), else 8-, 4- or 1-byte
- * elements.  SHIFT is for callers that see arbitrary offsets (the device
- * API, serving, plans, host-issued moves); the put/get pattern kernels keep
- * it off so that their aligned path's registers stay as they were (the
- * grid-scope kernel is already at the 128-register limit of its launch).
- * LONE marks a copy by one lane (lane 0 of 1), whose unaligned edges move
- * in wide pieces. */
-template <int U, bool NT, bool SHIFT = false, bool LONE = false>
-__device__ __forceinline__ void copy_bytes(uint8_t *d, const uint8_t *s, uint64_t n, uint64_t lane, uint64_t nl)
+__device__ __forceinline__ void copy_elems(uint8_t *d, const uint8_t *s, uint64_t n, uint64_t lane, uint64_t nl)
 {
     uint64_t x = (uintptr_t)d ^ (uintptr_t)s;
-    if ((x & 15) == 0) copy_aligned<v4u, U, NT, LONE>(d, s, n, lane, nl);
-    else if (SHIFT && n >= kShiftedMin) copy_shifted<U, NT>(d, s, n, lane, nl);
-    else if ((x & 7) == 0) copy_aligned<uint64_t, U, NT, LONE>(d, s, n, lane, nl);
-    else if ((x & 3) == 0) copy_aligned<uint32_t, U, NT, LONE>(d, s, n, lane, nl);
+    if ((x & 15) == 0) copy_aligned<v4u, U, NT>(d, s, n, lane, nl);
+    else if ((x & 7) == 0) copy_aligned<uint64_t, U, NT>(d, s, n, lane, nl);
+    else if ((x & 3) == 0) copy_aligned<uint32_t, U, NT>(d, s, n, lane, nl);
     else
         for (uint64_t i = lane; i < n; i += nl) d[i] = s[i];
+}
+
+/* A T at any address: gfx950 reads and writes global memory at any byte
+ * address (unaligned access mode, the platform's default), so these are one
+ * instruction, as for an aligned T. */
+template <bool NT, typename T>
+__device__ __forceinline__ T ld_any(const uint8_t *p)
+{
+    typedef T A __attribute__((aligned(1)));
+    return ld<NT>((const A *)p);
+}
+
+template <bool NT, typename T>
+__device__ __forceinline__ void st_any(uint8_t *p, T v)
+{
+    typedef T A __attribute__((aligned(1)));
+    if constexpr (NT) __builtin_nontemporal_store(v, (A *)p);
+    else *(A *)p = v;
+}
+
+/* Copy of n bytes by one lane.  Pieces of 16 bytes from the start, the last
+ * one ending at the last byte (it may repeat bytes of the one before); four
+ * loads in flight.  Below 16 bytes, two pieces of the widest size that fits
+ * (one when it fits exactly: an 8-byte message is one 8-byte move). */
+template <int U, bool NT>
+__device__ __forceinline__ void copy_lone(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n)
+{
+    if (n >= 16) {
+        uint64_t o = 0;
+        for (; o + 16 * U <= n; o += 16 * U) {
+            v4u r[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + o + 16 * u);
+#pragma unroll
+            for (int u = 0; u < U; ++u) st_any<NT, v4u>(d + o + 16 * u, r[u]);
+        }
+        if (o < n) {
+            v4u r[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (o + 16 * u < n) r[u] = ld_any<NT, v4u>(s + min(o + 16 * u, n - 16));
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (o + 16 * u < n) st_any<NT, v4u>(d + min(o + 16 * u, n - 16), r[u]);
+        }
+    } else if (n >= 8) {
+        const uint64_t a = ld_any<NT, uint64_t>(s), b = ld_any<NT, uint64_t>(s + n - 8);
+        st_any<NT, uint64_t>(d, a);
+        if (n > 8) st_any<NT, uint64_t>(d + n - 8, b);
+    } else if (n >= 4) {
+        const uint32_t a = ld_any<NT, uint32_t>(s), b = ld_any<NT, uint32_t>(s + n - 4);
+        st_any<NT, uint32_t>(d, a);
+        if (n > 4) st_any<NT, uint32_t>(d + n - 4, b);
+    } else if (n >= 2) {
+        const uint16_t a = ld_any<NT, uint16_t>(s), b = ld_any<NT, uint16_t>(s + n - 2);
+        st_any<NT, uint16_t>(d, a);
+        if (n > 2) st_any<NT, uint16_t>(d + n - 2, b);
+    } else if (n) {
+        *d = *s;
+    }
+}
+
+/* nv 16-byte vectors to an aligned destination from a source at any address,
+ * by nl lanes (this one is `lane`), U loads in flight per lane, also in the
+ * last, partly filled batch. */
+template <int U, bool NT>
+__device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__restrict__ s, uint64_t nv,
+                                          uint64_t lane, uint64_t nl)
+{
+    uint64_t i = lane;
+    for (; i + (uint64_t)(U - 1) * nl < nv; i += (uint64_t)U * nl) {
+        v4u r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + 16 * (i + (uint64_t)u * nl));
+#pragma unroll
+        for (int u = 0; u < U; ++u) st<NT>(d + i + (uint64_t)u * nl, r[u]);
+    }
+    if (i < nv) {
+        v4u r[U];
+#pragma unroll
+        for (int u = 0; u < U - 1; ++u)
+            if (i + (uint64_t)u * nl < nv) r[u] = ld_any<NT, v4u>(s + 16 * (i + (uint64_t)u * nl));
+#pragma unroll
+        for (int u = 0; u < U - 1; ++u)
+            if (i + (uint64_t)u * nl < nv) st<NT>(d + i + (uint64_t)u * nl, r[u]);
+    }
+}
+
+/* Copy n bytes with nl >= 2 cooperating lanes (this one is `lane`), at any
+ * alignment of either side.  n >= 16: the destination's 16-byte vectors that
+ * lie inside the message (stores stay aligned, loads take the source as it
+ * falls), and the first and the last 16 bytes where the destination's edges
+ * are not on a boundary; those overlap the vectors beside them and write the
+ * same bytes.  LONE marks a copy by one lane (lane 0 of 1).
+ *
+ * Bound by HBM for large messages and by that round trip for short ones.
+ * Measured with one wavefront per message, 4096 messages per PE, 64 PEs,
+ * U = 4: messages of 1501 bytes at addresses that disagree modulo 16 moved
+ * at 2.6 TB/s, against 0.44 with the narrower elements (down to bytes)
+ * that such a pair took before. */
+template <int U, bool NT, bool LONE = false>
+__device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n,
+                                           uint64_t lane, uint64_t nl)
+{
+    if constexpr (LONE) {
+        copy_lone<U, NT>(d, s, n);
+        return;
+    }
+    if (n < 16) {
+        for (uint64_t i = lane; i < n; i += nl) d[i] = s[i];
+        return;
+    }
+    const uint64_t head = (16 - ((uintptr_t)d & 15)) & 15;
+    const uint64_t nv = (n - head) / 16;
+    // The edges, by the lanes that a short message leaves idle.
+    const uint64_t eo = lane + 1 == nl ? n - 16 : 0;
+    const bool edge = lane + 1 == nl ? ((n - head) & 15) != 0 : lane + 2 == nl && head != 0;
+    v4u e;
+    if (edge) e = ld_any<NT, v4u>(s + eo);
+    copy_vecs<U, NT>((v4u *)(d + head), s + head, nv, lane, nl);
+    if (edge) st_any<NT, v4u>(d + eo, e);
 }
 
 __device__ __forceinline__ bool cmp_holds_u(uint64_t x, int cmp, uint64_t v)
@@ -537,7 +548,7 @@ __device__ __forceinline__ bool wg_agree(const shmem_dctx_t &ctx, bool ok, uint6
 __device__ __forceinline__ void shmem_putmem(const shmem_dctx_t &ctx, void *dest, const void *src, size_t n, int pe)
 {
     if (!vshmem_detail::rma_ok(ctx, dest, src, n, pe)) return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true, true>(shmem_ptr(ctx, (uint8_t *)dest, pe),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmem_ptr(ctx, (uint8_t *)dest, pe),
                                                                shmemx_local_ptr(ctx, (const uint8_t *)src), n, 0, 1);
 }
 __device__ __forceinline__ void shmem_putmem_nbi(const shmem_dctx_t &ctx, void *dest, const void *src, size_t n, int pe)
@@ -549,7 +560,7 @@ __device__ __forceinline__ void shmem_putmem_wave(const shmem_dctx_t &ctx, void 
     if (!vshmem_detail::wave_agree(ctx, vshmem_detail::rma_ok(ctx, dest, src, n, pe), VSHMEM_U64(dest),
                                    VSHMEM_U64(src), n, (uint64_t)pe))
         return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmem_ptr(ctx, (uint8_t *)dest, pe),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false>(shmem_ptr(ctx, (uint8_t *)dest, pe),
                                                          shmemx_local_ptr(ctx, (const uint8_t *)src), n,
                                                          __lane_id(), 64);
 }
@@ -562,7 +573,7 @@ __device__ __forceinline__ void shmem_putmem_nbi_wg(const shmem_dctx_t &ctx, voi
     if (!vshmem_detail::wg_agree(ctx, vshmem_detail::rma_ok(ctx, dest, src, n, pe), VSHMEM_U64(dest), VSHMEM_U64(src),
                                  n, (uint64_t)pe))
         return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmem_ptr(ctx, (uint8_t *)dest, pe),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false>(shmem_ptr(ctx, (uint8_t *)dest, pe),
                                                          shmemx_local_ptr(ctx, (const uint8_t *)src), n,
                                                          threadIdx.x, blockDim.x);
 }
@@ -580,7 +591,7 @@ __device__ __forceinline__ void shmemx_putmem_grid(const shmem_dctx_t &ctx, void
     if (!vshmem_detail::wg_agree(ctx, vshmem_detail::rma_ok(ctx, dest, src, n, pe), VSHMEM_U64(dest), VSHMEM_U64(src),
                                  n, ((uint64_t)(uint32_t)nwgs << 32) | (uint32_t)pe))
         return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmem_ptr(ctx, (uint8_t *)dest, pe),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false>(shmem_ptr(ctx, (uint8_t *)dest, pe),
                                                          shmemx_local_ptr(ctx, (const uint8_t *)src), n,
                                                          (uint64_t)rank * blockDim.x + threadIdx.x,
                                                          (uint64_t)nwgs * blockDim.x);
@@ -590,7 +601,7 @@ __device__ __forceinline__ void shmemx_putmem_grid(const shmem_dctx_t &ctx, void
 __device__ __forceinline__ void shmem_getmem(const shmem_dctx_t &ctx, void *dest, const void *src, size_t n, int pe)
 {
     if (!vshmem_detail::rma_ok(ctx, dest, src, n, pe)) return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true, true>(shmemx_local_ptr(ctx, (uint8_t *)dest),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmemx_local_ptr(ctx, (uint8_t *)dest),
                                                                shmem_ptr(ctx, (const uint8_t *)src, pe), n, 0, 1);
 }
 __device__ __forceinline__ void shmem_getmem_nbi(const shmem_dctx_t &ctx, void *dest, const void *src, size_t n, int pe)
@@ -602,7 +613,7 @@ __device__ __forceinline__ void shmem_getmem_wave(const shmem_dctx_t &ctx, void 
     if (!vshmem_detail::wave_agree(ctx, vshmem_detail::rma_ok(ctx, dest, src, n, pe), VSHMEM_U64(dest),
                                    VSHMEM_U64(src), n, (uint64_t)pe))
         return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmemx_local_ptr(ctx, (uint8_t *)dest),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false>(shmemx_local_ptr(ctx, (uint8_t *)dest),
                                                          shmem_ptr(ctx, (const uint8_t *)src, pe), n,
                                                          __lane_id(), 64);
 }
@@ -615,7 +626,7 @@ __device__ __forceinline__ void shmem_getmem_nbi_wg(const shmem_dctx_t &ctx, voi
     if (!vshmem_detail::wg_agree(ctx, vshmem_detail::rma_ok(ctx, dest, src, n, pe), VSHMEM_U64(dest), VSHMEM_U64(src),
                                  n, (uint64_t)pe))
         return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmemx_local_ptr(ctx, (uint8_t *)dest),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false>(shmemx_local_ptr(ctx, (uint8_t *)dest),
                                                          shmem_ptr(ctx, (const uint8_t *)src, pe), n,
                                                          threadIdx.x, blockDim.x);
 }
@@ -630,7 +641,7 @@ __device__ __forceinline__ void shmemx_getmem_grid(const shmem_dctx_t &ctx, void
     if (!vshmem_detail::wg_agree(ctx, vshmem_detail::rma_ok(ctx, dest, src, n, pe), VSHMEM_U64(dest), VSHMEM_U64(src),
                                  n, ((uint64_t)(uint32_t)nwgs << 32) | (uint32_t)pe))
         return;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, true>(shmemx_local_ptr(ctx, (uint8_t *)dest),
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false>(shmemx_local_ptr(ctx, (uint8_t *)dest),
                                                          shmem_ptr(ctx, (const uint8_t *)src, pe), n,
                                                          (uint64_t)rank * blockDim.x + threadIdx.x,
                                                          (uint64_t)nwgs * blockDim.x);
@@ -922,36 +933,50 @@ __device__ __forceinline__ uint64_t member_stride(const shmem_dctx_t &ctx, const
 }
 
 // Copy one source range to the same place on every team member (d0 is
-// member 0's copy, members pstride apart).  Aligned ranges go through a
+// member 0's copy, members pstride apart).  The range goes through a
 // register tile: each lane loads kMcastTile 16-byte vectors once, then the
 // whole tile is written to one member after another, starting at a member
 // that depends on the worker so that concurrent work-groups spread over
 // the members.  Long contiguous writes per member page measured about 10%
 // faster on MI355X than writing every vector to all members in turn.
+// The vectors are the destination's (the same on every member, the member
+// stride being a multiple of 16), the loads take the source as it falls, and
+// up to two 16-byte pieces at the edges (or, below 16 bytes, single bytes)
+// are dealt to the threads member by member.
 template <bool NT>
 __device__ __forceinline__ void multicast(uint8_t *d0, uint64_t pstride, int P, const uint8_t *src, uint64_t len,
                                           uint32_t worker)
 {
-    if ((((uintptr_t)src | (uintptr_t)d0 | len) & 15) == 0) {
-        const v4u *s = (const v4u *)src;
-        const uint64_t nv = len / 16, bd = blockDim.x;
-        for (uint64_t i0 = threadIdx.x; i0 < nv; i0 += kMcastTile * bd) {
-            v4u r[kMcastTile];
+    const uint32_t bd = blockDim.x;
+    if (len < 16) {
+        for (uint32_t q = threadIdx.x; q < (uint32_t)P * (uint32_t)len; q += bd) {
+            const uint32_t p = q / (uint32_t)len, i = q - p * (uint32_t)len;
+            d0[p * pstride + i] = src[i];
+        }
+        return;
+    }
+    const uint64_t head = (16 - ((uintptr_t)d0 & 15)) & 15, nv = (len - head) / 16;
+    const bool tail = ((len - head) & 15) != 0;
+    if (head || tail)
+        for (uint32_t q = threadIdx.x; q < 2 * (uint32_t)P; q += bd)
+            if ((q & 1) ? tail : head != 0) {
+                const uint64_t o = (q & 1) ? len - 16 : 0;
+                st_any<NT, v4u>(d0 + (q >> 1) * pstride + o, ld_any<true, v4u>(src + o));
+            }
+    for (uint64_t i0 = threadIdx.x; i0 < nv; i0 += (uint64_t)kMcastTile * bd) {
+        const uint8_t *s = src + head + 16 * i0;
+        v4u r[kMcastTile];
+#pragma unroll
+        for (int u = 0; u < kMcastTile; ++u)
+            if (i0 + u * bd < nv) r[u] = ld_any<true, v4u>(s + 16 * u * bd);
+        int p = (int)(worker % (uint32_t)P);
+        for (int k = 0; k < P; ++k) {
+            v4u *d = (v4u *)(d0 + head + (uint64_t)p * pstride) + i0;
 #pragma unroll
             for (int u = 0; u < kMcastTile; ++u)
-                if (i0 + u * bd < nv) r[u] = ld<true>(s + i0 + u * bd);
-            int p = (int)(worker % (uint32_t)P);
-            for (int k = 0; k < P; ++k) {
-                v4u *d = (v4u *)(d0 + (uint64_t)p * pstride);
-#pragma unroll
-                for (int u = 0; u < kMcastTile; ++u)
-                    if (i0 + u * bd < nv) st<NT>(d + i0 + u * bd, r[u]);
-                if (++p == P) p = 0;
-            }
+                if (i0 + u * bd < nv) st<NT>(d + u * bd, r[u]);
+            if (++p == P) p = 0;
         }
-    } else {
-        for (int p = 0; p < P; ++p)
-            copy_bytes<VSHMEM_COPY_UNROLL, NT>(d0 + p * pstride, src, len, threadIdx.x, blockDim.x);
     }
 }
 
@@ -1029,7 +1054,7 @@ __device__ __forceinline__ void alltoall(const shmem_dctx_t &ctx, const shmemx_d
             const uint64_t p = blk / P;   // destination member
             const uint64_t q = blk % P;   // source member
             const uint64_t off = (t - blk * nch) * chunk;
-            copy_bytes<U, NT>(D0 + p * ps + q * n + off, S0 + q * ps + p * n + off, min(chunk, n - off), lane, g);
+            copy_elems<U, NT>(D0 + p * ps + q * n + off, S0 + q * ps + p * n + off, min(chunk, n - off), lane, g);
         }
     }
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);

@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(MAXT) k_rma_pattern(shmemx_dctx_pub_t c, const
             j = copy_msgs4<vshmem_detail::v4u, NT>(D, S, (uint32_t)(msg / 16), sstep, dstep, j, nmsg, nl);
         else if (msg <= 16 && (al & 7) == 0)
             j = copy_msgs4<uint64_t, NT>(D, S, (uint32_t)(msg / 8), sstep, dstep, j, nmsg, nl);
-        for (; j < nmsg; j += nl) vshmem_detail::copy_bytes<U, NT, false, true>(D + j * dstep, S + j * sstep, msg, 0, 1);
+        for (; j < nmsg; j += nl) vshmem_detail::copy_bytes<U, NT, true>(D + j * dstep, S + j * sstep, msg, 0, 1);
     } else if constexpr (SCOPE == SHMEMX_SCOPE_WAVE) {
         const uint64_t waves = blockDim.x / 64;
         const uint64_t nw = (uint64_t)wgs_per_pe * waves;
