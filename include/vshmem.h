@@ -379,7 +379,9 @@ typedef struct shmemx_launch {
  * and the destination on targets[p]; for SHMEMX_OP_GET the source is on
  * targets[p] and the destination on p.  Each PE ends with quiet.
  * Scope THREAD: each lane issues whole messages; WAVE: each wavefront; WG:
- * each work-group; GRID: all work-groups of the PE share each message.
+ * each work-group; GRID: all work-groups of the PE share each message.  The
+ * messages are non-blocking until the quiet: which lanes of a wavefront or a
+ * work-group move the bytes of its messages is the library's choice.
  * targets: DEVICE pointer to npes int32.  Ranges must lie in the user part
  * of the heap and destinations must not overlap (the result would be
  * undefined); SHMEMX_ERR_ARG otherwise.

@@ -7,77 +7,119 @@ using namespace vshmem;
 
 namespace {
 
-// Thread-scope messages of m <= 2 elements of V each (addresses, size and
-// steps all multiples of sizeof(V)), one lane per message: the lane loads
-// four messages before it stores any of them, as a run of non-blocking puts
-// may, so that their round trips overlap instead of following one another.
-// (Messages of three or four vectors measured slower this way than one at a
-// time.)  Returns the first message index it did not move.
-template <typename V, bool NT>
-__device__ __forceinline__ uint64_t copy_msgs4(uint8_t *D, const uint8_t *S, uint32_t m, uint64_t sstep,
-                                               uint64_t dstep, uint64_t j, uint64_t nmsg, uint64_t nl)
+// Messages m0 .. m1 - 1 (addresses step apart) by nl lanes (whole
+// wavefronts), this one `lane`:
+// their pieces of sizeof(V) bytes form one index space that the lanes walk,
+// U pieces in flight each, so a message of a few pieces leaves no lane idle
+// and costs no round trip of its own.  A message's last piece ends at its
+// last byte (it may repeat bytes of the one before).  msg >= sizeof(V).
+template <typename V, int U, bool NT>
+__device__ __forceinline__ void copy_run(uint8_t *D, const uint8_t *S, uint64_t msg, uint64_t sstep, uint64_t dstep,
+                                         uint64_t m0, uint64_t m1, uint32_t lane, uint32_t nl)
 {
-    constexpr int G = 4;
-    for (; j + (G - 1) * nl < nmsg; j += G * nl) {
-        V r[G][2];
+    constexpr uint32_t A = sizeof(V);
+    const uint32_t ppm = (uint32_t)((msg + A - 1) / A), last = (uint32_t)msg - A;
+    const uint64_t n = (m1 - m0) * ppm;
+    // A wavefront's U pieces per lane are one contiguous run of 64 U; the
+    // next batch is the unit's U * nl pieces further.  A step of x pieces is
+    // x / ppm messages and x % ppm pieces.
+    constexpr uint32_t w = 64;
+    const uint32_t first = (lane >> 6) * (U * w) + (lane & 63), far = U * nl - (U - 1) * w;
+    const uint32_t wj = w / ppm, wr = w % ppm, fj = far / ppm, fr = far % ppm;
+    uint32_t r = first % ppm;
+    S += (m0 + first / ppm) * sstep;
+    D += (m0 + first / ppm) * dstep;
+    auto step = [&](uint32_t j, uint32_t q) {
+        r += q;
+        if (r >= ppm) {
+            r -= ppm;
+            ++j;
+        }
+        S += j * sstep;
+        D += j * dstep;
+    };
+    for (uint64_t k = first; k < n; k += (uint64_t)U * nl) {
+        V v[U];
+        uint8_t *to[U];
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const V *s = (const V *)(S + (j + g * nl) * sstep);
-            r[g][0] = vshmem_detail::ld<NT>(s);
-            if (m > 1) r[g][1] = vshmem_detail::ld<NT>(s + 1);
+        for (int u = 0; u < U; ++u) {
+            if (u) step(wj, wr);
+            const uint32_t o = min(r * A, last);
+            to[u] = D + o;
+            if (k + (uint64_t)u * w < n) v[u] = vshmem_detail::ld_any<NT, V>(S + o);
         }
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            V *d = (V *)(D + (j + g * nl) * dstep);
-            vshmem_detail::st<NT>(d, r[g][0]);
-            if (m > 1) vshmem_detail::st<NT>(d + 1, r[g][1]);
-        }
+        for (int u = 0; u < U; ++u)
+            if (k + (uint64_t)u * w < n) vshmem_detail::st_any<NT, V>(to[u], v[u]);
+        step(fj, fr);
     }
-    return j;
 }
 
 // Every virtual PE p issues nmsg messages to targets[p] at the given scope,
-// then quiets.  Work-group w acts for PE w / wgs_per_pe.  MAXT is the
-// largest work-group the instance accepts: launches of at most 256 threads
-// take an instance compiled for that size, whose register budget (up to 512
-// per lane) holds the 8-deep grid-scope body without spilling; under the
-// 1024-thread bound the same body needs 60 bytes of scratch per lane.
+// then quiets.  Work-group w acts for PE w / wgs_per_pe.  A unit (a
+// wavefront at thread and wavefront scope, a work-group, the PE's whole
+// share of the grid) takes a run of consecutive messages, all of them
+// non-blocking until the quiet:
+//   - messages that follow one another without a gap on both sides move as
+//     the one range that they are;
+//   - otherwise, messages too short to fill one batch of the unit (U 16-byte
+//     vectors per lane) are walked together, piece by piece;
+//   - longer ones are copied one after another.
+// One message at a time costs a round trip to memory per message while most
+// lanes idle: with one wavefront per 1 KiB message, 64 PEs x 8192 messages
+// took 422 us (2.5 TB/s) and take 198 (5.4); one lane per 64 B message, 64
+// PEs x 16384, 49 us (2.7) and 33 (4.1); 1501 B at odd addresses, 64 PEs x
+// 4096, 302 us (2.6) and 147 (5.3).  Messages that are whole batches stay
+// one at a time, dealt round robin: a wavefront's 4 KiB messages moved at
+// 6.0 TB/s so and at 5.8 as one contiguous range per wavefront.  MAXT is the
+// largest work-group the instance accepts.
 template <int SCOPE, bool IS_PUT, bool NT, int U, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_rma_pattern(shmemx_dctx_pub_t c, const int32_t *__restrict__ targets,
                                                       uint64_t src_off, uint64_t dst_off, uint64_t msg, uint64_t nmsg,
                                                       uint64_t sstep, uint64_t dstep, int wgs_per_pe)
 {
-    const int pe = blockIdx.x / wgs_per_pe;
-    const int rank = blockIdx.x - pe * wgs_per_pe;
+    const uint32_t pe = blockIdx.x / (uint32_t)wgs_per_pe;
+    const uint32_t rank = blockIdx.x - pe * (uint32_t)wgs_per_pe;
     const int tgt = targets[pe];
     if (tgt < 0) return;
     // Source and destination PE of every message of this PE.
-    const int spe = IS_PUT ? pe : tgt;
-    const int dpe = IS_PUT ? tgt : pe;
+    const int spe = IS_PUT ? (int)pe : tgt;
+    const int dpe = IS_PUT ? tgt : (int)pe;
     const uint8_t *S = c.base + (uint64_t)spe * c.stride + src_off;
     uint8_t *D = c.base + (uint64_t)dpe * c.stride + dst_off;
-    if constexpr (SCOPE == SHMEMX_SCOPE_THREAD) {
-        const uint64_t nl = (uint64_t)wgs_per_pe * blockDim.x;
-        uint64_t j = (uint64_t)rank * blockDim.x + threadIdx.x;
-        const uint64_t al = (uintptr_t)S | (uintptr_t)D | msg | sstep | dstep;
-        if (msg <= 32 && (al & 15) == 0)
-            j = copy_msgs4<vshmem_detail::v4u, NT>(D, S, (uint32_t)(msg / 16), sstep, dstep, j, nmsg, nl);
-        else if (msg <= 16 && (al & 7) == 0)
-            j = copy_msgs4<uint64_t, NT>(D, S, (uint32_t)(msg / 8), sstep, dstep, j, nmsg, nl);
-        for (; j < nmsg; j += nl) vshmem_detail::copy_bytes<U, NT, true>(D + j * dstep, S + j * sstep, msg, 0, 1);
-    } else if constexpr (SCOPE == SHMEMX_SCOPE_WAVE) {
-        const uint64_t waves = blockDim.x / 64;
-        const uint64_t nw = (uint64_t)wgs_per_pe * waves;
-        for (uint64_t j = (uint64_t)rank * waves + threadIdx.x / 64; j < nmsg; j += nw)
-            vshmem_detail::copy_bytes<U, NT>(D + j * dstep, S + j * sstep, msg, __lane_id(), 64);
+    uint32_t unit = 0, units = 1, lane, nl;
+    if constexpr (SCOPE <= SHMEMX_SCOPE_WAVE) {
+        const uint32_t waves = blockDim.x / 64;
+        unit = rank * waves + threadIdx.x / 64;
+        units = (uint32_t)wgs_per_pe * waves;
+        lane = __lane_id();
+        nl = 64;
     } else if constexpr (SCOPE == SHMEMX_SCOPE_WG) {
-        for (uint64_t j = rank; j < nmsg; j += wgs_per_pe)
-            vshmem_detail::copy_bytes<U, NT>(D + j * dstep, S + j * sstep, msg, threadIdx.x, blockDim.x);
+        unit = rank;
+        units = (uint32_t)wgs_per_pe;
+        lane = threadIdx.x;
+        nl = blockDim.x;
     } else {
-        const uint64_t lane = (uint64_t)rank * blockDim.x + threadIdx.x;
-        const uint64_t nl = (uint64_t)wgs_per_pe * blockDim.x;
-        for (uint64_t j = 0; j < nmsg; ++j)
-            vshmem_detail::copy_bytes<U, NT>(D + j * dstep, S + j * sstep, msg, lane, nl);
+        lane = rank * blockDim.x + threadIdx.x;
+        nl = (uint32_t)wgs_per_pe * blockDim.x;
+    }
+    const uint64_t q = nmsg / units, rem = nmsg - q * units;
+    const uint64_t m0 = unit * q + min<uint64_t>(unit, rem), m1 = m0 + q + (unit < rem);
+    if (m0 < m1) {
+        const uint64_t batch = 16ull * U * nl;
+        const bool batches = msg % batch == 0 && (((uintptr_t)D | dstep) & 15) == 0;
+        if (sstep == msg && dstep == msg && !batches)
+            vshmem_detail::copy_bytes<U, NT>(D + m0 * msg, S + m0 * msg, (m1 - m0) * msg, lane, nl);
+        else if (msg >= 16 && !batches && msg < min<uint64_t>(8 * batch, 1u << 30))
+            copy_run<vshmem_detail::v4u, 4, NT>(D, S, msg, sstep, dstep, m0, m1, lane, nl);
+        else if (msg >= 16)
+            for (uint64_t j = unit; j < nmsg; j += units)
+                vshmem_detail::copy_bytes<U, NT>(D + j * dstep, S + j * sstep, msg, lane, nl);
+        else if (msg >= 8)
+            copy_run<uint64_t, 4, NT>(D, S, msg, sstep, dstep, m0, m1, lane, nl);
+        else
+            for (uint64_t j = m0 + lane; j < m1; j += nl)
+                vshmem_detail::copy_lone<1, NT>(D + j * dstep, S + j * sstep, msg);
     }
     vshmem_detail::release_wg_at_exit();   // quiet
 }

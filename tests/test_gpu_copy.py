@@ -38,3 +38,31 @@ def test_every_alignment_pair(scope, flags):
                             init[p, so + j * (pitch + 1):so + j * (pitch + 1) + n]
             assert np.array_equal(download(init.shape[1]), ref), n
         assert_no_device_errors()
+
+
+@pytest.mark.parametrize("scope", [W.SCOPE_THREAD, W.SCOPE_WAVE, W.SCOPE_WG, W.SCOPE_GRID])
+def test_runs_of_messages(scope):
+    """Packed and spaced runs, with more, as many and fewer messages than
+    units, around a unit's batch (64, 128 or 384 lanes of four vectors)."""
+    npes, area = 3, 1 << 20
+    with heap(npes, 4 * area) as v:
+        base = v.offset(v.malloc(2 * area + 4096))
+        init = W.heap_fill(0xA22 + scope, npes, base + 2 * area + 4096)
+        tgt = device_array(np.array([1, 2, 0], dtype=np.int32))
+        launch = v.launch_cfg(wgs_per_pe=3, wg_size=128)
+        for n in (1, 7, 8, 13, 16, 40, 1000, 4096, 4097, 8192, 24576, 32768, 40000, 98304):
+            for count in (1, 2, 7, 100):
+                for sgap, dgap, ss, ds in ((0, 0, 0, 0), (0, 0, 5, 0), (0, 16, 0, 0), (3, 9, 1, 2), (-n, 0, 4, 4)):
+                    if count * (n + 16) > area:
+                        continue
+                    upload(init)
+                    so, do = base + ss, base + area + ds
+                    v.rma_pattern(W.OP_GET, scope, tgt, so, do, n, count, n + sgap, n + dgap, launch=launch)
+                    ref = init.copy()
+                    for p in range(npes):
+                        q = (p + 1) % npes
+                        for j in range(count):
+                            s, d = so + j * (n + sgap), do + j * (n + dgap)
+                            ref[p, d:d + n] = init[q, s:s + n]
+                    assert np.array_equal(download(init.shape[1]), ref), (n, count, sgap, dgap, ss, ds)
+        assert_no_device_errors()
