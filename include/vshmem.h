@@ -358,8 +358,9 @@ int shmemx_set_wait_timeout_ns(uint64_t ns);
  * unit of work handed to one work-group when a message or collective is
  * split across work-groups (multiple of 16).  Zero fields take defaults;
  * for the team collectives wgs_per_pe = 0 means one work-group per member
- * per 512 KiB the member writes, at most one per CU over the team and never
- * more than stay co-resident. */
+ * per 16 KiB the member writes, at most one per CU over the team and never
+ * more than stay co-resident.  For the team collectives chunk_bytes is the
+ * largest such unit: smaller blocks and even shares are cut smaller. */
 typedef struct shmemx_launch {
     int32_t wgs_per_pe;
     int32_t wg_size;

@@ -218,32 +218,6 @@ __device__ __forceinline__ void copy_body(V *__restrict__ d, const V *__restrict
     for (; i < nv; i += nl) st<NT>(d + i, ld<NT>(s + i));
 }
 
-/* Copy n bytes in the widest elements (16, 8, 4 bytes) on whose size source
- * and destination agree, else in bytes, with byte edges. */
-template <typename V, int U, bool NT>
-__device__ __forceinline__ void copy_aligned(uint8_t *__restrict__ d, const uint8_t *__restrict__ s,
-                                             uint64_t n, uint64_t lane, uint64_t nl)
-{
-    constexpr uint64_t A = sizeof(V);
-    uint64_t head = (A - ((uintptr_t)d & (A - 1))) & (A - 1);
-    if (head > n) head = n;
-    for (uint64_t i = lane; i < head; i += nl) d[i] = s[i];
-    uint64_t nv = (n - head) / A;
-    copy_body<V, U, NT>((V *)(d + head), (const V *)(s + head), nv, lane, nl);
-    for (uint64_t i = head + nv * A + lane; i < n; i += nl) d[i] = s[i];
-}
-
-template <int U, bool NT>
-__device__ __forceinline__ void copy_elems(uint8_t *d, const uint8_t *s, uint64_t n, uint64_t lane, uint64_t nl)
-{
-    uint64_t x = (uintptr_t)d ^ (uintptr_t)s;
-    if ((x & 15) == 0) copy_aligned<v4u, U, NT>(d, s, n, lane, nl);
-    else if ((x & 7) == 0) copy_aligned<uint64_t, U, NT>(d, s, n, lane, nl);
-    else if ((x & 3) == 0) copy_aligned<uint32_t, U, NT>(d, s, n, lane, nl);
-    else
-        for (uint64_t i = lane; i < n; i += nl) d[i] = s[i];
-}
-
 /* A T at any address: gfx950 reads and writes global memory at any byte
  * address (unaligned access mode, the platform's default), so these are one
  * instruction, as for an aligned T. */
@@ -913,6 +887,10 @@ __device__ __forceinline__ void shmem_barrier_all_wg(const shmem_dctx_t &ctx)
 }
 
 /* ---------------------------------------------------------- collectives */
+/* The functions in vshmem_detail move and combine the data; they hold no
+ * barrier.  The device collectives below open and close them with one of
+ * the team.  A kernel that is one whole collective needs neither: its launch
+ * follows, and its end precedes, everything else on its stream. */
 namespace vshmem_detail {
 
 constexpr uint64_t kCollChunk = 256ull << 10;   // bytes per task: broadcast, fcollect, alltoall
@@ -992,84 +970,148 @@ __device__ __forceinline__ void multicast(uint8_t *d0, uint64_t pstride, int P, 
     }
 }
 
+// x / d, in 32 bits when both fit (a 64-bit division is a long sequence).
+__device__ __forceinline__ uint64_t udiv(uint64_t x, uint64_t d)
+{
+    return ((x | d) >> 32) == 0 ? (uint32_t)x / (uint32_t)d : x / d;
+}
+
+// How a multicast of Q source ranges of n bytes to P members is cut into
+// tasks: chunks of a range (all of one size, whole 4 KiB pages of the
+// destination's lines where they are long) times groups of members.  With
+// enough ranges and chunks of the launch's size a task writes its chunk to
+// every member, and the chunks shrink until the last round of tasks is full.
+// With less than half a task per worker, chunks are at most 64 KiB (four
+// vectors per lane of 1024) and the members are split as well, then the
+// chunks down to 16 KiB (one vector per lane): re-reading a chunk for each
+// group of members costs little, most of the traffic being the writes, and
+// an idle CU costs its share.  One 1024-thread work-group per CU, 64 members:
+// a broadcast of 1 MiB took 137 us as four tasks of 256 KiB and takes 17;
+// fcollect of 300000 bytes 258 us in two rounds, the second a quarter full,
+// and 248 in one.  13 members, 256 MiB: chunks of even size but off the line
+// boundaries 1099 us, on them 759.
+struct McastSplit {
+    uint64_t chunk, nch;     // bytes per chunk, chunks per range
+    uint32_t per, groups;    // members per task, member groups
+};
+__device__ __forceinline__ McastSplit mcast_split(uint64_t n, uint32_t Q, uint32_t P, uint32_t workers, uint64_t chunk)
+{
+    uint64_t c = chunk, k = udiv(n + c - 1, c);
+    if (2 * k * Q < workers) {
+        c = min<uint64_t>(c, 64u << 10);
+        k = udiv(n + c - 1, c);
+        for (; c > (16u << 10) && k * Q * P < workers; c >>= 1) k *= 2;
+    }
+    // Whole rounds: as many groups as leave every task a worker of its own,
+    // then as many chunks as fill the last round.
+    uint32_t g = 1;
+    if (k * Q < workers) {
+        g = min(P, workers / ((uint32_t)k * Q));
+        k = max<uint64_t>(k, workers / (g * Q));
+    } else {
+        k = udiv(udiv(k * Q + workers - 1, workers) * workers, Q);
+    }
+    McastSplit m;
+    const uint64_t even = udiv(n + k - 1, k), line = even >= (16u << 10) ? 4096 : 16;
+    m.chunk = (even + line - 1) & ~(line - 1);
+    m.nch = udiv(n + m.chunk - 1, m.chunk);
+    m.per = (P + g - 1) / g;
+    m.groups = (P + m.per - 1) / m.per;
+    return m;
+}
+
+// The Q ranges of a broadcast (Q = 1) or fcollect (Q = P): range q is n
+// bytes at src + q * sstep and goes to dest + q * n on every member.
+// Neighbouring tasks are chunks of one range for one group: the work-groups
+// that run together write neighbouring runs of the same members (with the
+// groups of one chunk as neighbours, 13 members, 256 MiB: 919 us against
+// 742).
+template <bool NT>
+__device__ __forceinline__ void multicast_all(uint8_t *D, uint64_t ps, uint32_t P, const uint8_t *src, uint64_t sstep,
+                                              uint32_t Q, uint64_t n, const Workers &W, uint64_t chunk)
+{
+    const McastSplit m = mcast_split(n, Q, P, W.n, chunk);
+    const uint64_t ntask = m.nch * Q * m.groups;
+    for (uint64_t t = W.w; t < ntask; t += W.n) {
+        const uint64_t r = udiv(t, m.nch), g = udiv(r, Q), q = r - g * Q;
+        const uint64_t off = (t - r * m.nch) * m.chunk;
+        const uint32_t p0 = (uint32_t)g * m.per;
+        multicast<NT>(D + p0 * ps + q * n + off, ps, (int)min(m.per, P - p0), src + q * sstep + off,
+                      min(m.chunk, n - off), W.w);
+    }
+}
+
 // Every member's dest[0, n) <- member root's src[0, n), root included.
 template <bool NT>
 __device__ __forceinline__ void broadcast(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
                                           const void *src, uint64_t n, int root, int rank, int nwgs, uint64_t chunk)
 {
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
-    const Workers W = team_workers(ctx, team, rank, nwgs);
-    const uint8_t *S = (const uint8_t *)src + (uint64_t)shmemx_team_pe(team, root) * ctx.c.stride;
-    uint8_t *D = member0(ctx, team, dest);
-    const uint64_t ps = member_stride(ctx, team);
-    const uint64_t ntask = (n + chunk - 1) / chunk;
-    for (uint64_t t = W.w; t < ntask; t += W.n) {
-        const uint64_t off = t * chunk;
-        multicast<NT>(D + off, ps, team.size, S + off, min(chunk, n - off), W.w);
-    }
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
+    if (n == 0) return;
+    multicast_all<NT>(member0(ctx, team, dest), member_stride(ctx, team), (uint32_t)team.size,
+                      (const uint8_t *)src + (uint64_t)shmemx_team_pe(team, root) * ctx.c.stride, 0, 1, n,
+                      team_workers(ctx, team, rank, nwgs), chunk);
 }
 
-// Every member's dest[q*n, (q+1)*n) <- member q's src[0, n).
+// Member p's block q <- a block of member q, n bytes each: block p of its
+// source (alltoall) or its only one (fcollect of small blocks).  Nothing
+// here needs a work-group together, so a task is one chunk of one block and
+// goes to one wavefront: chunks of whole batches (U 16-byte vectors per
+// lane), about eight to a wavefront where the blocks allow it, so that
+// wavefronts end together whatever the block size.  Blocks shorter than a
+// batch go to a group of g lanes, the smallest power of two that covers one
+// in a pass.  64 members, one 1024-thread work-group per CU: blocks of 300000
+// bytes took 466 us cut into even chunks per work-group (whose last, partly
+// filled batch is a round trip of its own) and take 437, blocks of 100001
+// bytes 166 and 159, 1 MiB 1480 and 1460.  Consecutive tasks go to different work-groups first, so a few
+// tiny blocks per member still spread over every work-group.
+template <bool NT, int U, bool ONE>
+__device__ __forceinline__ void pair_blocks(uint8_t *D0, const uint8_t *S0, uint64_t ps, uint32_t P, uint64_t n,
+                                            const Workers &W, uint64_t chunk)
+{
+    constexpr uint64_t kPass = 16ull * U, kBatch = 64 * kPass;   // bytes per lane and per wavefront in one pass
+    const uint64_t share = udiv(n * P * P, (uint64_t)W.n * (blockDim.x / 64) * 8);
+    const uint64_t task = min(min(chunk, n), max(kBatch, min<uint64_t>(share / kBatch * kBatch, 64u << 10)));
+    uint32_t g = 2;
+    while (g < 64 && g * kPass < task) g <<= 1;
+    const uint64_t nch = udiv(n + task - 1, task);
+    const uint64_t ntask = nch * P * P;
+    const uint32_t mine = threadIdx.x / g, lane = threadIdx.x % g, groups = blockDim.x / g;
+    if (mine >= groups) return;   // threads past the last whole group
+    for (uint64_t t = (uint64_t)mine * W.n + W.w; t < ntask; t += (uint64_t)W.n * groups) {
+        const uint64_t blk = udiv(t, nch);
+        const uint32_t p = (uint32_t)udiv(blk, P);              // destination member
+        const uint32_t q = (uint32_t)(blk - (uint64_t)p * P);   // source member
+        const uint64_t off = (t - blk * nch) * task;
+        copy_bytes<U, NT>(D0 + p * ps + q * n + off, S0 + q * ps + (ONE ? 0 : p * n) + off, min(task, n - off), lane,
+                          g);
+    }
+}
+
+// Every member's dest[q*n, (q+1)*n) <- member q's src[0, n).  Blocks shorter
+// than kPairMax go from each source to each destination, many at once; longer
+// ones are read once per group of members.
+constexpr uint64_t kPairMax = 16ull << 10;
 template <bool NT>
 __device__ __forceinline__ void fcollect(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
                                          const void *src, uint64_t n, int rank, int nwgs, uint64_t chunk)
 {
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
+    if (n == 0) return;
     const Workers W = team_workers(ctx, team, rank, nwgs);
     const uint8_t *S0 = member0(ctx, team, src);
     uint8_t *D = member0(ctx, team, dest);
     const uint64_t ps = member_stride(ctx, team);
-    const uint64_t nch = (n + chunk - 1) / chunk;
-    const uint64_t ntask = nch * (uint64_t)team.size;
-    for (uint64_t t = W.w; t < ntask; t += W.n) {
-        const uint64_t q = t / nch;
-        const uint64_t off = (t - q * nch) * chunk;
-        multicast<NT>(D + q * n + off, ps, team.size, S0 + q * ps + off, min(chunk, n - off), W.w);
-    }
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
+    if (n < kPairMax) pair_blocks<NT, 4, true>(D, S0, ps, (uint32_t)team.size, n, W, chunk);
+    else multicast_all<NT>(D, ps, (uint32_t)team.size, S0, ps, (uint32_t)team.size, n, W, chunk);
 }
 
-// Member p's dest[q*n, (q+1)*n) <- member q's src[p*n, (p+1)*n).  A task is
-// one chunk of one block.  A task shorter than half of one pass of the
-// work-group (U 16-byte vectors per lane) goes to a group of g lanes: the
-// smallest power of two, at most a wavefront, that covers it in one pass.
-// A work-group then copies blockDim/g small blocks at once; one task per
-// work-group would leave most lanes idle and pay a memory round trip per
-// block.  Consecutive tasks go to different work-groups first, so a few
-// tiny blocks per member still spread over every work-group.
+// Member p's dest[q*n, (q+1)*n) <- member q's src[p*n, (p+1)*n).
 template <bool NT, int U>
 __device__ __forceinline__ void alltoall(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
                                          const void *src, uint64_t n, int rank, int nwgs, uint64_t chunk)
 {
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
-    const Workers W = team_workers(ctx, team, rank, nwgs);
-    const uint8_t *S0 = member0(ctx, team, src);
-    uint8_t *D0 = member0(ctx, team, dest);
-    const uint64_t ps = member_stride(ctx, team);
-    const uint64_t P = (uint64_t)team.size;
-    const uint64_t nch = (n + chunk - 1) / chunk;
-    const uint64_t ntask = nch * P * P;
-    constexpr uint64_t kPass = 16ull * U;   // bytes per lane per pass
-    const uint64_t task = min(chunk, n);
-    uint32_t g = blockDim.x;
-    if (task * 2 < kPass * blockDim.x) {
-        const uint64_t need = (task + kPass - 1) / kPass;
-        g = 1;
-        while (g < 64 && g < need) g <<= 1;
-    }
-    const uint32_t groups = blockDim.x / g;   // threads past groups * g stay idle
-    if (threadIdx.x < groups * g) {
-        const uint64_t lane = threadIdx.x % g;
-        for (uint64_t t = (uint64_t)(threadIdx.x / g) * W.n + W.w; t < ntask; t += (uint64_t)W.n * groups) {
-            const uint64_t blk = t / nch;
-            const uint64_t p = blk / P;   // destination member
-            const uint64_t q = blk % P;   // source member
-            const uint64_t off = (t - blk * nch) * chunk;
-            copy_elems<U, NT>(D0 + p * ps + q * n + off, S0 + q * ps + p * n + off, min(chunk, n - off), lane, g);
-        }
-    }
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
+    if (n == 0) return;
+    pair_blocks<NT, U, false>(member0(ctx, team, dest), member0(ctx, team, src), member_stride(ctx, team),
+                              (uint32_t)team.size, n, team_workers(ctx, team, rank, nwgs), chunk);
 }
 
 // TREE in streaming form.  Pushing x_0, x_1, ... keeps, for every set bit j
@@ -1257,8 +1299,7 @@ __device__ __forceinline__ void reduce_singles(int P, uint64_t pstride, const ui
 // member's page, so each address translation serves K KiB instead of 1
 // KiB: the member walk visits 2P pages per vector, more than a CU's
 // first-level translation cache holds.  LEVELS bounds the team size
-// (2^LEVELS - 1 members).  Returns SHMEMX_ERR_UNSUPPORTED, without
-// synchronising, for teams larger than that.
+// (2^LEVELS - 1 members); larger teams get SHMEMX_ERR_UNSUPPORTED.
 template <class CODEC, class OP, bool NT, int K = 1, int LEVELS = kTreeLevels>
 __device__ __forceinline__ int reduce(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
                                       const void *src, uint64_t nelem, int rank, int nwgs, uint64_t chunk)
@@ -1267,7 +1308,6 @@ __device__ __forceinline__ int reduce(const shmem_dctx_t &ctx, const shmemx_dtea
     constexpr int E = CODEC::E;
     constexpr int B = kRedBatch / K > 0 ? kRedBatch / K : 1;   // members per load batch
     if (team.size >= (1 << LEVELS)) return SHMEMX_ERR_UNSUPPORTED;
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     const Workers W = team_workers(ctx, team, rank, nwgs);
     const int P = team.size;
     const uint64_t pstride = member_stride(ctx, team);
@@ -1329,7 +1369,6 @@ __device__ __forceinline__ int reduce(const shmem_dctx_t &ctx, const shmemx_dtea
         }
     }
     reduce_singles<CODEC, OP>(P, pstride, s0, d0, nelem, h, h + nvec * 16 / CODEC::ES, W);
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
 
@@ -1358,7 +1397,6 @@ __device__ __forceinline__ void reduce_waves(const shmem_dctx_t &ctx, const shme
     using A = typename CODEC::A;
     constexpr int E = CODEC::E;
     __shared__ A part[2][kRedWaveMax][E][64];
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     const Workers W = team_workers(ctx, team, rank, nwgs);
     const int P = team.size;
     const uint32_t waves = blockDim.x / 64, w = threadIdx.x / 64, lane = __lane_id();
@@ -1425,7 +1463,6 @@ __device__ __forceinline__ void reduce_waves(const shmem_dctx_t &ctx, const shme
         buf ^= 1;
     }
     reduce_singles<CODEC, OP>(P, pstride, s0, d0, nelem, h, h + nvec * 16 / CODEC::ES, W);
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
 }
 
 } // namespace vshmem_detail
@@ -1476,7 +1513,9 @@ __device__ __forceinline__ int shmemx_broadcastmem_grid(const shmem_dctx_t &ctx,
     if (!vshmem_detail::coll_ok(ctx, team, dest, n, src, n, root >= 0 && root < team.size && rank >= 0 && rank < nwgs,
                                 n, ((uint64_t)(uint32_t)nwgs << 32) | (uint32_t)root))
         return SHMEMX_ERR_ARG;
+    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     vshmem_detail::broadcast<false>(ctx, team, dest, src, n, root, rank, nwgs, vshmem_detail::kCollChunk);
+    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
 __device__ __forceinline__ int shmem_broadcastmem_wg(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
@@ -1490,7 +1529,9 @@ __device__ __forceinline__ int shmemx_fcollectmem_grid(const shmem_dctx_t &ctx, 
     if (!vshmem_detail::coll_ok(ctx, team, dest, (uint64_t)n * team.size, src, n, rank >= 0 && rank < nwgs, n,
                                 (uint64_t)nwgs))
         return SHMEMX_ERR_ARG;
+    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     vshmem_detail::fcollect<false>(ctx, team, dest, src, n, rank, nwgs, vshmem_detail::kCollChunk);
+    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
 __device__ __forceinline__ int shmem_fcollectmem_wg(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
@@ -1504,7 +1545,9 @@ __device__ __forceinline__ int shmemx_alltoallmem_grid(const shmem_dctx_t &ctx, 
     if (!vshmem_detail::coll_ok(ctx, team, dest, (uint64_t)n * team.size, src, (uint64_t)n * team.size,
                                 rank >= 0 && rank < nwgs, n, (uint64_t)nwgs))
         return SHMEMX_ERR_ARG;
+    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     vshmem_detail::alltoall<true, 8>(ctx, team, dest, src, n, rank, nwgs, vshmem_detail::kCollChunk);
+    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
 __device__ __forceinline__ int shmem_alltoallmem_wg(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
@@ -1521,8 +1564,12 @@ __device__ __forceinline__ int shmem_alltoallmem_wg(const shmem_dctx_t &ctx, con
         if (!vshmem_detail::coll_ok(ctx, team, dest, nreduce * sizeof(T), src, nreduce * sizeof(T),               \
                                     rank >= 0 && rank < nwgs, nreduce, (uint64_t)nwgs))                            \
             return SHMEMX_ERR_ARG;                                                                                 \
-        return vshmem_detail::reduce<vshmem_detail::CODEC, vshmem_detail::OP, true>(                               \
+        if (team.size >= (1 << vshmem_detail::kTreeLevels)) return SHMEMX_ERR_UNSUPPORTED;                         \
+        shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);                                                         \
+        (void)vshmem_detail::reduce<vshmem_detail::CODEC, vshmem_detail::OP, true>(                                \
             ctx, team, dest, src, nreduce, rank, nwgs, vshmem_detail::kRedChunk);                                  \
+        shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);                                                         \
+        return 0;                                                                                                  \
     }
 /* The grid forms carry the shmemx_ prefix; the _wg forms are OpenSHMEM names. */
 #define VSHMEM_DEVICE_REDUCE_WG(NAME, GRIDNAME, T)                                                                   \

@@ -27,8 +27,12 @@ struct Geo {
     int wgs_per_pe;
 };
 
-// The library's launches are user kernels of the device collectives: work-
-// group b acts for team member b / wgs_per_pe, as its rank b % wgs_per_pe.
+// The library's launches run the device collectives' bodies, without their
+// opening and closing team barriers: nothing inside a collective depends on
+// another work-group's stores, the launch follows all earlier work of its
+// stream, and its end completes every store.  With them a reduction of 16 fp32
+// elements over 64 PEs took 15.6 us, and takes 10.6 without.  Work-group b acts for team
+// member b / wgs_per_pe, as its rank b % wgs_per_pe.
 struct Caller {
     shmem_dctx_t ctx;
     void *dst;
@@ -88,36 +92,42 @@ __global__ void __launch_bounds__(64 * vshmem_detail::kRedWaveMax) k_reduce_wave
 }
 
 // ------------------------------------------------------------- launching
-// Bytes a member writes per automatically added work-group: below this a
-// second work-group per member costs more in barrier arrivals than it saves
-// in copying (64 PEs: alltoall of 4 KiB blocks took 16 us with one
-// work-group per member and 25 us with four; 16 KiB blocks 41 us with two,
-// 47 with four and 56 with one).
-constexpr uint64_t kAutoBytesPerWg = 512ull << 10;
+// Bytes a member writes per automatically added work-group: one pass of 1024
+// lanes.  A further work-group costs its dispatch only, now that it is no
+// barrier arrival: 64 PEs, alltoall of 4 KiB blocks takes 7.4 us with four
+// per member (the rate at which the host launches), broadcast of 64 KiB 7.1
+// with four; both had one, between barriers, and took 15.4 and 46.5.
+constexpr uint64_t kAutoBytesPerWg = 16ull << 10;
 
-// Launch a kernel whose work-groups synchronise with each other.  When the
-// caller left wgs_per_pe at 0, about one work-group per CU over the team,
-// fewer when each member writes little (bytes_per_member), and never more
-// than stay co-resident.
+// Wavefronts per CU that a launch of each collective may count on.  The
+// launches do not wait for one another, so these are the interface's limits
+// on explicit shapes, not the kernels' occupancy: a grid that the device
+// collectives could not hold resident is refused in both forms.
+constexpr int kWavesBroadcast = 16, kWavesFcollect = 20, kWavesAlltoallDeep = 20, kWavesAlltoall = 32;
+constexpr int kWavesReduce = 20, kWavesReduceBf16 = 12, kWavesReduce2 = 16, kWavesReduce2Bf16 = 8;
+constexpr int kWavesReduceSplit = 16, kWavesReduceSplitBf16 = 12;
+
+// Launch a collective's kernel.  When the caller left wgs_per_pe at 0, about
+// one work-group per CU over the team, fewer when each member writes little
+// (bytes_per_member), and never more than `waves` wavefronts per CU hold.
 template <typename K, typename... Args>
-int launch_team_kernel(K kernel, Geo &g, int wg, hipStream_t s, bool auto_wgs, uint64_t bytes_per_member,
+int launch_team_kernel(K kernel, int waves, Geo &g, int wg, hipStream_t s, bool auto_wgs, uint64_t bytes_per_member,
                        Args... args)
 {
+    const int per_cu = std::max(1, waves * 64 / wg);
     if (auto_wgs) {
         // About one work-group per CU: in measurements on MI355X, streaming
         // kernels reached higher HBM bandwidth with one wide work-group per
         // CU than with the grid filled to its occupancy limit.
         // Only the CUs the progress kernel leaves free count.
-        int64_t cap = 0;
-        if (int rc = coresident_capacity(kernel, wg, &cap)) return rc;
-        const int64_t free_cus = st().num_cus - progress_reserved_cus();
+        const int64_t free_cus = std::max(0, st().num_cus - progress_reserved_cus());
         const uint64_t by_bytes = (bytes_per_member + kAutoBytesPerWg - 1) / kAutoBytesPerWg;
         const int64_t want = std::max<int64_t>(
             1, std::min<int64_t>(free_cus / g.team.size, (int64_t)std::min<uint64_t>(by_bytes, 1u << 20)));
-        g.wgs_per_pe = (int)std::max<int64_t>(1, std::min<int64_t>(want, cap / g.team.size));
+        g.wgs_per_pe = (int)std::max<int64_t>(1, std::min<int64_t>(want, per_cu * free_cus / g.team.size));
     }
     const int grid = g.wgs_per_pe * g.team.size;
-    if (int rc = check_coresident(kernel, grid, wg, "team collective")) return rc;
+    if (int rc = check_resident(per_cu, grid, wg, "team collective")) return rc;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(wg), 0, s, g, args...);
     VSHMEM_HIP(hipGetLastError());
     return SHMEMX_OK;
@@ -163,8 +173,8 @@ int shmemx_broadcastmem_launch(shmem_team_t team, void *dest, const void *src, s
     g.n = n;
     const bool aw = !launch || launch->wgs_per_pe == 0;
     if (L.flags & SHMEMX_LAUNCH_NONTEMPORAL)
-        return launch_team_kernel(k_broadcast<true>, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n, root);
-    return launch_team_kernel(k_broadcast<false>, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n, root);
+        return launch_team_kernel(k_broadcast<true>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n, root);
+    return launch_team_kernel(k_broadcast<false>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n, root);
 }
 
 int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, size_t n, const shmemx_launch_t *launch,
@@ -185,8 +195,8 @@ int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, si
     g.n = n;
     const bool aw = !launch || launch->wgs_per_pe == 0;
     if (L.flags & SHMEMX_LAUNCH_NONTEMPORAL)
-        return launch_team_kernel(k_fcollect<true>, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n * tsize);
-    return launch_team_kernel(k_fcollect<false>, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n * tsize);
+        return launch_team_kernel(k_fcollect<true>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n * tsize);
+    return launch_team_kernel(k_fcollect<false>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n * tsize);
 }
 
 int shmemx_alltoallmem_launch(shmem_team_t team, void *dest, const void *src, size_t n, const shmemx_launch_t *launch,
@@ -210,10 +220,10 @@ int shmemx_alltoallmem_launch(shmem_team_t team, void *dest, const void *src, si
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0, deep = (L.flags & SHMEMX_LAUNCH_DEEP) != 0;
     hipStream_t hs = (hipStream_t)stream;
     const uint64_t wb = (uint64_t)n * tsize;
-    if (nt && deep) return launch_team_kernel(k_alltoall<true, 8>, g, L.wg_size, hs, aw, wb);
-    if (nt) return launch_team_kernel(k_alltoall<true, 4>, g, L.wg_size, hs, aw, wb);
-    if (deep) return launch_team_kernel(k_alltoall<false, 8>, g, L.wg_size, hs, aw, wb);
-    return launch_team_kernel(k_alltoall<false, 4>, g, L.wg_size, hs, aw, wb);
+    if (nt && deep) return launch_team_kernel(k_alltoall<true, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw, wb);
+    if (nt) return launch_team_kernel(k_alltoall<true, 4>, kWavesAlltoall, g, L.wg_size, hs, aw, wb);
+    if (deep) return launch_team_kernel(k_alltoall<false, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw, wb);
+    return launch_team_kernel(k_alltoall<false, 4>, kWavesAlltoall, g, L.wg_size, hs, aw, wb);
 }
 
 int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const void *src, size_t nreduce,
@@ -252,20 +262,20 @@ int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const
     hipStream_t s = (hipStream_t)stream;
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
     const uint64_t wb = nreduce * es;
-#define VSHMEM_RED_K(K, CODEC)                                                                              \
-    if (op == SHMEMX_RED_SUM)                                                                               \
-        return nt ? launch_team_kernel(K<CODEC, OpSum, true>, g, L.wg_size, s, aw, wb)                      \
-                  : launch_team_kernel(K<CODEC, OpSum, false>, g, L.wg_size, s, aw, wb);                    \
-    return nt ? launch_team_kernel(K<CODEC, OpMax, true>, g, L.wg_size, s, aw, wb)                          \
-              : launch_team_kernel(K<CODEC, OpMax, false>, g, L.wg_size, s, aw, wb);
+    const bool bf = dtype == SHMEMX_DT_BF16;
+#define VSHMEM_RED_K(K, W, CODEC)                                                                           \
+    do {                                                                                                    \
+        const int w_ = bf ? W##Bf16 : W;                                                                    \
+        if (op == SHMEMX_RED_SUM)                                                                           \
+            return nt ? launch_team_kernel(K<CODEC, OpSum, true>, w_, g, L.wg_size, s, aw, wb)              \
+                      : launch_team_kernel(K<CODEC, OpSum, false>, w_, g, L.wg_size, s, aw, wb);            \
+        return nt ? launch_team_kernel(K<CODEC, OpMax, true>, w_, g, L.wg_size, s, aw, wb)                  \
+                  : launch_team_kernel(K<CODEC, OpMax, false>, w_, g, L.wg_size, s, aw, wb);                \
+    } while (0)
 #define VSHMEM_RED(CODEC)                                                                                   \
-    if (waves) {                                                                                            \
-        VSHMEM_RED_K(k_reduce_waves, CODEC)                                                                 \
-    }                                                                                                       \
-    if (two) {                                                                                              \
-        VSHMEM_RED_K(k_reduce2, CODEC)                                                                      \
-    }                                                                                                       \
-    VSHMEM_RED_K(k_reduce, CODEC)
+    if (waves) VSHMEM_RED_K(k_reduce_waves, kWavesReduceSplit, CODEC);                                      \
+    if (two) VSHMEM_RED_K(k_reduce2, kWavesReduce2, CODEC);                                                 \
+    VSHMEM_RED_K(k_reduce, kWavesReduce, CODEC);
     if (dtype == SHMEMX_DT_INT64) {
         VSHMEM_RED(CodecI64)
     } else if (dtype == SHMEMX_DT_FP32) {

@@ -140,11 +140,8 @@ int coresident_capacity(K kernel, int wg, int64_t *cap)
 // running progress kernel, SHMEMX_ERR_ARG when they never fit.  Only the
 // library's own persistent kernel is accounted for; kernels the caller runs
 // on other streams at the same time are the caller's to keep apart.
-template <typename K>
-int check_coresident(K kernel, int64_t grid, int wg, const char *what)
+inline int check_resident(int per_cu, int64_t grid, int wg, const char *what)
 {
-    int per_cu = 0;
-    if (int rc = blocks_per_cu(kernel, wg, &per_cu)) return rc;
     const int reserved = progress_reserved_cus();
     const int64_t idle_cap = (int64_t)per_cu * st().num_cus;
     const int64_t cap = (int64_t)per_cu * (st().num_cus > reserved ? st().num_cus - reserved : 0);
@@ -160,6 +157,14 @@ int check_coresident(K kernel, int64_t grid, int wg, const char *what)
                      what, (long long)grid, wg, per_cu, st().num_cus);
     if (st().debug) fprintf(stderr, "vshmem: %s: work-groups cannot be co-resident\n", what);
     return SHMEMX_ERR_ARG;
+}
+
+template <typename K>
+int check_coresident(K kernel, int64_t grid, int wg, const char *what)
+{
+    int per_cu = 0;
+    if (int rc = blocks_per_cu(kernel, wg, &per_cu)) return rc;
+    return check_resident(per_cu, grid, wg, what);
 }
 
 }  // namespace vshmem
