@@ -107,25 +107,29 @@ constexpr int kWavesBroadcast = 16, kWavesFcollect = 20, kWavesAlltoallDeep = 20
 constexpr int kWavesReduce = 20, kWavesReduceBf16 = 12, kWavesReduce2 = 16, kWavesReduce2Bf16 = 8;
 constexpr int kWavesReduceSplit = 16, kWavesReduceSplitBf16 = 12;
 
-// Launch a collective's kernel.  When the caller left wgs_per_pe at 0, about
-// one work-group per CU over the team, fewer when each member writes little
-// (bytes_per_member), and never more than `waves` wavefronts per CU hold.
+// CUs the progress kernel leaves free.
+int64_t free_cus() { return std::max(0, st().num_cus - progress_reserved_cus()); }
+
+// Work-groups over the team of a data-movement collective whose members
+// write bytes_per_member each: about one per CU, fewer when that is little.
+// In measurements on MI355X, streaming copies reached higher HBM bandwidth
+// with one wide work-group per CU than with the grid filled to its occupancy
+// limit.
+int64_t movement_wgs(const Geo &g, uint64_t bytes_per_member)
+{
+    const uint64_t by_bytes = (bytes_per_member + kAutoBytesPerWg - 1) / kAutoBytesPerWg;
+    return std::min<int64_t>(free_cus(), (int64_t)std::min<uint64_t>(by_bytes, 1u << 20) * g.team.size);
+}
+
+// Launch a collective's kernel.  When the caller left wgs_per_pe at 0, with
+// about auto_wgs work-groups, a whole number per member, and never more than
+// `waves` wavefronts per CU hold.
 template <typename K, typename... Args>
-int launch_team_kernel(K kernel, int waves, Geo &g, int wg, hipStream_t s, bool auto_wgs, uint64_t bytes_per_member,
-                       Args... args)
+int launch_team_kernel(K kernel, int waves, Geo &g, int wg, hipStream_t s, int64_t auto_wgs, Args... args)
 {
     const int per_cu = std::max(1, waves * 64 / wg);
-    if (auto_wgs) {
-        // About one work-group per CU: in measurements on MI355X, streaming
-        // kernels reached higher HBM bandwidth with one wide work-group per
-        // CU than with the grid filled to its occupancy limit.
-        // Only the CUs the progress kernel leaves free count.
-        const int64_t free_cus = std::max(0, st().num_cus - progress_reserved_cus());
-        const uint64_t by_bytes = (bytes_per_member + kAutoBytesPerWg - 1) / kAutoBytesPerWg;
-        const int64_t want = std::max<int64_t>(
-            1, std::min<int64_t>(free_cus / g.team.size, (int64_t)std::min<uint64_t>(by_bytes, 1u << 20)));
-        g.wgs_per_pe = (int)std::max<int64_t>(1, std::min<int64_t>(want, per_cu * free_cus / g.team.size));
-    }
+    if (g.wgs_per_pe == 0)
+        g.wgs_per_pe = (int)std::max<int64_t>(1, std::min<int64_t>(auto_wgs, per_cu * free_cus()) / g.team.size);
     const int grid = g.wgs_per_pe * g.team.size;
     if (int rc = check_resident(per_cu, grid, wg, "team collective")) return rc;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(wg), 0, s, g, args...);
@@ -149,7 +153,7 @@ int make_geo(shmem_team_t team, const void *dest, const void *src, uint64_t dst_
     if (g.dst_off == UINT64_MAX || g.src_off == UINT64_MAX) return SHMEMX_ERR_ARG;
     g.c = pub();
     g.chunk = L.chunk_bytes;
-    g.wgs_per_pe = L.wgs_per_pe;
+    g.wgs_per_pe = launch ? launch->wgs_per_pe : 0;   // 0: the launch's own choice
     return SHMEMX_OK;
 }
 
@@ -171,10 +175,9 @@ int shmemx_broadcastmem_launch(shmem_team_t team, void *dest, const void *src, s
         return rc;
     }
     g.n = n;
-    const bool aw = !launch || launch->wgs_per_pe == 0;
     if (L.flags & SHMEMX_LAUNCH_NONTEMPORAL)
-        return launch_team_kernel(k_broadcast<true>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n, root);
-    return launch_team_kernel(k_broadcast<false>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n, root);
+        return launch_team_kernel(k_broadcast<true>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, n), root);
+    return launch_team_kernel(k_broadcast<false>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, n), root);
 }
 
 int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, size_t n, const shmemx_launch_t *launch,
@@ -193,10 +196,9 @@ int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, si
         return rc;
     }
     g.n = n;
-    const bool aw = !launch || launch->wgs_per_pe == 0;
     if (L.flags & SHMEMX_LAUNCH_NONTEMPORAL)
-        return launch_team_kernel(k_fcollect<true>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n * tsize);
-    return launch_team_kernel(k_fcollect<false>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, aw, (uint64_t)n * tsize);
+        return launch_team_kernel(k_fcollect<true>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, (uint64_t)n * tsize));
+    return launch_team_kernel(k_fcollect<false>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, (uint64_t)n * tsize));
 }
 
 int shmemx_alltoallmem_launch(shmem_team_t team, void *dest, const void *src, size_t n, const shmemx_launch_t *launch,
@@ -216,14 +218,13 @@ int shmemx_alltoallmem_launch(shmem_team_t team, void *dest, const void *src, si
         return rc;
     }
     g.n = n;
-    const bool aw = !launch || launch->wgs_per_pe == 0;
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0, deep = (L.flags & SHMEMX_LAUNCH_DEEP) != 0;
     hipStream_t hs = (hipStream_t)stream;
-    const uint64_t wb = (uint64_t)n * tsize;
-    if (nt && deep) return launch_team_kernel(k_alltoall<true, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw, wb);
-    if (nt) return launch_team_kernel(k_alltoall<true, 4>, kWavesAlltoall, g, L.wg_size, hs, aw, wb);
-    if (deep) return launch_team_kernel(k_alltoall<false, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw, wb);
-    return launch_team_kernel(k_alltoall<false, 4>, kWavesAlltoall, g, L.wg_size, hs, aw, wb);
+    const int64_t aw = movement_wgs(g, (uint64_t)n * tsize);
+    if (nt && deep) return launch_team_kernel(k_alltoall<true, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw);
+    if (nt) return launch_team_kernel(k_alltoall<true, 4>, kWavesAlltoall, g, L.wg_size, hs, aw);
+    if (deep) return launch_team_kernel(k_alltoall<false, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw);
+    return launch_team_kernel(k_alltoall<false, 4>, kWavesAlltoall, g, L.wg_size, hs, aw);
 }
 
 int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const void *src, size_t nreduce,
@@ -238,15 +239,13 @@ int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const
     // Work-groups of up to 256 threads: one lane folds every member
     // (k_reduce).  Larger ones (up to 512): the members are split over the
     // wavefronts (k_reduce_waves), for teams of at most 8 members per
-    // wavefront.  On MI355X the two measured the same at their best shapes
-    // (the split form needs two work-groups per CU to get there), so the
-    // default stays with the first.
+    // wavefront.
     shmemx_launch_t L0 = launch ? *launch : shmemx_launch_t{0, 256, 16ull << 10, SHMEMX_LAUNCH_NONTEMPORAL, 0};
     if (L0.wg_size == 0) L0.wg_size = 256;
     if (!rc) rc = make_geo(team, dest, src, nreduce * es, nreduce * es, &L0, 256, g, L);
     // In place is allowed; partial overlap is not.
     if (!rc && g.dst_off != g.src_off && overlap(g.dst_off, nreduce * es, g.src_off, nreduce * es)) rc = SHMEMX_ERR_ARG;
-    const bool waves = L.wg_size > 256;
+    bool waves = L.wg_size > 256;
     // SHMEMX_LAUNCH_DEEP: two vectors per lane (teams of up to 127 members).
     const bool two = !waves && (L.flags & SHMEMX_LAUNCH_DEEP) && g.team.size < 128;
     if (!rc && (L.wg_size > 64 * vshmem_detail::kRedWaveMax || L.chunk_bytes == 0 ||
@@ -258,19 +257,39 @@ int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const
         return rc;
     }
     g.n = nreduce;
-    const bool aw = !launch || launch->wgs_per_pe == 0;
     hipStream_t s = (hipStream_t)stream;
-    const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
-    const uint64_t wb = nreduce * es;
     const bool bf = dtype == SHMEMX_DT_BF16;
+    const int64_t P = g.team.size, nvec = (int64_t)(nreduce * es / 16);
+    // Without a shape from the caller: a reduction with fewer vectors than
+    // half the lanes of a 256-thread work-group per CU leaves lanes idle and
+    // is a chain of P / 8 load batches in each of the others.  Splitting the
+    // members over wavefronts makes it one batch: 64 members, fp32, 16384
+    // vectors 13.2 -> 9.6 us, bf16, 8192 vectors 16.3 -> 8.5, 16 elements
+    // 10.7 -> 7.6 (the launch); at 65536 vectors the split form is the slower
+    // one (37 us against 25), and so it is for 13 members, two batches (9.8
+    // against 7.7 at 16384 vectors).
+    const int split_cu = (bf ? kWavesReduceSplitBf16 : kWavesReduceSplit) * 64 / 512;
+    if (!waves && !two && (!launch || (launch->wgs_per_pe == 0 && launch->wg_size == 0 && launch->chunk_bytes == 0)) &&
+        P >= 32 && P <= 64 && 2 * nvec <= free_cus() * 256 && split_cu * free_cus() >= P) {
+        waves = true;
+        L.wg_size = 512;
+        g.chunk = 1024;   // one tile of 64 vectors
+    }
+    // Work-groups: two per CU, while each still has 128 vectors (64 members,
+    // fp32, 2^20 elements: 91.6 us with two per CU, 94.5 with one; 2^22
+    // elements 358 and 355, so above 2048 vectors per CU one); split over
+    // wavefronts, one per tile step.
+    const int64_t per_step = waves ? 64 * std::max<int64_t>(1, 8 / ((P + 7) / 8)) : 128;
+    const int64_t aw = std::min<int64_t>((nvec <= 2048 * free_cus() ? 2 : 1) * free_cus(), (nvec + per_step * P - 1) / (per_step * P) * P);
+    const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
 #define VSHMEM_RED_K(K, W, CODEC)                                                                           \
     do {                                                                                                    \
         const int w_ = bf ? W##Bf16 : W;                                                                    \
         if (op == SHMEMX_RED_SUM)                                                                           \
-            return nt ? launch_team_kernel(K<CODEC, OpSum, true>, w_, g, L.wg_size, s, aw, wb)              \
-                      : launch_team_kernel(K<CODEC, OpSum, false>, w_, g, L.wg_size, s, aw, wb);            \
-        return nt ? launch_team_kernel(K<CODEC, OpMax, true>, w_, g, L.wg_size, s, aw, wb)                  \
-                  : launch_team_kernel(K<CODEC, OpMax, false>, w_, g, L.wg_size, s, aw, wb);                \
+            return nt ? launch_team_kernel(K<CODEC, OpSum, true>, w_, g, L.wg_size, s, aw)              \
+                      : launch_team_kernel(K<CODEC, OpSum, false>, w_, g, L.wg_size, s, aw);            \
+        return nt ? launch_team_kernel(K<CODEC, OpMax, true>, w_, g, L.wg_size, s, aw)                  \
+                  : launch_team_kernel(K<CODEC, OpMax, false>, w_, g, L.wg_size, s, aw);                \
     } while (0)
 #define VSHMEM_RED(CODEC)                                                                                   \
     if (waves) VSHMEM_RED_K(k_reduce_waves, kWavesReduceSplit, CODEC);                                      \

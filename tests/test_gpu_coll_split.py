@@ -4,6 +4,7 @@ sizes that are not multiples of 16, for teams that are no power of two."""
 import numpy as np
 import pytest
 
+import oracle
 import workload as W
 from tests.gpu_helpers import assert_no_device_errors, download, heap, upload
 
@@ -50,4 +51,32 @@ def test_movement_at_split_edges(kind, npes, team, launch):
                         for q in range(P):
                             ref[p, b + q * n:b + (q + 1) * n] = init[pes[q], a + k * n:a + (k + 1) * n]
                 assert np.array_equal(download(init.shape[1]), ref), (n, ss, ds)
+        assert_no_device_errors()
+
+
+@pytest.mark.parametrize("npes", [9, 40, 70])   # one lane per vector; members over wavefronts; blocks of 64 in the edges
+@pytest.mark.parametrize("dt", [oracle.DT_INT64, oracle.DT_FP32, oracle.DT_BF16])
+def test_reductions_at_every_offset(dt, npes):
+    """Sources and destinations at different offsets from a 16-byte boundary,
+    and counts around the single elements at the edges and the shares of a
+    work-group: bit-exact against the oracle, nothing else written."""
+    es = {oracle.DT_INT64: 8, oracle.DT_FP32: 4, oracle.DT_BF16: 2}[dt]
+    kmax = 33000
+    with heap(npes, 1 << 20) as v:
+        src, dst = v.malloc(kmax * es + 64), v.malloc(kmax * es + 64)
+        so, do = v.offset(src), v.offset(dst)
+        region = do + kmax * es + 64
+        gen = {oracle.DT_INT64: W.coll_i64, oracle.DT_FP32: W.coll_f32, oracle.DT_BF16: W.coll_bf16}[dt]
+        rows = np.stack([np.ascontiguousarray(gen(0xD0 + npes, p, kmax)).view(np.uint8) for p in range(npes)])
+        for n in (1, 5, 16 // es, 31, 1000, kmax):
+            for a, b in ((0, 0), (es, es), (0, es), (2 * es, 0), (16 - es, es)):
+                for launch in (None, v.launch_cfg(wgs_per_pe=1, wg_size=64)):
+                    init = W.heap_fill(0xD1, npes, region)
+                    init[:, so + a:so + a + n * es] = rows[:, :n * es]
+                    upload(init)
+                    rop = oracle.RO_MAX if n == 31 else oracle.RO_SUM
+                    v.reduce(dt, rop, dst + b, src + a, n, launch=launch)
+                    ref = init.copy()
+                    oracle.reduce(ref, dt, rop, do + b, so + a, n)
+                    assert np.array_equal(download(region), ref), (n, a, b, launch is None)
         assert_no_device_errors()
