@@ -236,6 +236,10 @@ __device__ __forceinline__ void st_any(uint8_t *p, T v)
     else *(A *)p = v;
 }
 
+/* The loads before this line are issued before it: the compiler would sink
+ * a load whose value only a conditional store uses into the condition. */
+__device__ __forceinline__ void loads_issued() { asm volatile("" ::: "memory"); }
+
 /* Copy of n bytes by one lane.  Pieces of 16 bytes from the start, the last
  * one ending at the last byte (it may repeat bytes of the one before); four
  * loads in flight.  Below 16 bytes, two pieces of the widest size that fits
@@ -255,11 +259,9 @@ __device__ __forceinline__ void copy_lone(uint8_t *__restrict__ d, const uint8_t
         if (o < n) {
             v4u r[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (o + 16 * u < n) r[u] = ld_any<NT, v4u>(s + min(o + 16 * u, n - 16));
+            for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + min(o + 16 * u, n - 16));
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (o + 16 * u < n) st_any<NT, v4u>(d + min(o + 16 * u, n - 16), r[u]);
+            for (int u = 0; u < U; ++u) st_any<NT, v4u>(d + min(o + 16 * u, n - 16), r[u]);
         }
     } else if (n >= 8) {
         const uint64_t a = ld_any<NT, uint64_t>(s), b = ld_any<NT, uint64_t>(s + n - 8);
@@ -280,8 +282,12 @@ __device__ __forceinline__ void copy_lone(uint8_t *__restrict__ d, const uint8_t
 
 /* nv 16-byte vectors to an aligned destination from a source at any address,
  * by nl lanes (this one is `lane`), U loads in flight per lane, also in the
- * last, partly filled batch. */
-template <int U, bool NT>
+ * last, partly filled batch.  AGAIN: a lane's loads past the end read the
+ * last vector again, none under a condition of its own.  In the batches'
+ * executors the compiler put a wait after each conditional load, a round trip
+ * per vector (the 4-PE mixed program as a plan 34.8 us, and 32.6 with AGAIN);
+ * in the copy kernels it does not, and the repeated loads cost up to 8%. */
+template <int U, bool NT, bool AGAIN = false>
 __device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__restrict__ s, uint64_t nv,
                                           uint64_t lane, uint64_t nl)
 {
@@ -302,15 +308,17 @@ __device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__
 #pragma unroll
         for (int u = 0; u < U; ++u) st<NT>(d + i + u * w, r[u]);
     }
+    // The rest, in one batch.
     const uint64_t i = nb + lane;
     if (i < nv) {
         v4u r[U];
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (i + (uint64_t)u * nl < nv) r[u] = ld_any<NT, v4u>(s + 16 * (i + (uint64_t)u * nl));
+            if (AGAIN || i + u * nl < nv) r[u] = ld_any<NT, v4u>(s + 16 * (AGAIN ? min(i + u * nl, nv - 1) : i + u * nl));
+        if (AGAIN) loads_issued();
 #pragma unroll
         for (int u = 0; u < U; ++u)
-            if (i + (uint64_t)u * nl < nv) st<NT>(d + i + (uint64_t)u * nl, r[u]);
+            if (i + u * nl < nv) st<NT>(d + i + u * nl, r[u]);
     }
 }
 
@@ -328,7 +336,7 @@ __device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__
  * elements (down to bytes) that such a pair took before.  16 MiB messages by
  * 1024 threads, aligned, U = 8: 6.1 TB/s, against 5.7 with every nl-th
  * vector instead of contiguous runs per wavefront. */
-template <int U, bool NT, bool LONE = false>
+template <int U, bool NT, bool LONE = false, bool AGAIN = false>
 __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n,
                                            uint64_t lane, uint64_t nl)
 {
@@ -347,7 +355,7 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
     const bool edge = lane + 1 == nl ? ((n - head) & 15) != 0 : lane + 2 == nl && head != 0;
     v4u e;
     if (edge) e = ld_any<NT, v4u>(s + eo);
-    copy_vecs<U, NT>((v4u *)(d + head), s + head, nv, lane, nl);
+    copy_vecs<U, NT, AGAIN>((v4u *)(d + head), s + head, nv, lane, nl);
     if (edge) st_any<NT, v4u>(d + eo, e);
 }
 
@@ -922,6 +930,32 @@ __device__ __forceinline__ uint64_t member_stride(const shmem_dctx_t &ctx, const
     return (uint64_t)team.stride * ctx.c.stride;
 }
 
+// A multicast of n <= T * blockDim.x vectors, loaded once, then written to
+// one member after another, starting at a member that depends on the worker.
+// Loads past the end read the last vector again, none under a condition of
+// its own (copy_vecs tells why): broadcast of 1 MiB to 64 members, chunks of
+// 64 KiB to four of them per task, 17.4 us through the loop of whole tiles
+// below, 16.2 so.  For few members, where the loads' latency counts: with 64
+// per task the loop is the faster one (16 MiB 178 us against 182).
+template <bool NT, int T>
+__device__ __forceinline__ void mcast_small(uint8_t *d0, uint64_t pstride, int P, const uint8_t *s, uint32_t n,
+                                            uint32_t worker)
+{
+    const uint32_t i = threadIdx.x, bd = blockDim.x;
+    v4u r[T];
+#pragma unroll
+    for (int u = 0; u < T; ++u) r[u] = ld_any<true, v4u>(s + 16u * min(i + u * bd, n - 1));
+    loads_issued();
+    int p = (int)(worker % (uint32_t)P);
+    for (int k = 0; k < P; ++k) {
+        uint8_t *d = d0 + (uint64_t)p * pstride;
+#pragma unroll
+        for (int u = 0; u < T; ++u)
+            if (i + u * bd < n) st<NT>((v4u *)(d + 16u * (i + u * bd)), r[u]);
+        if (++p == P) p = 0;
+    }
+}
+
 // Copy one source range to the same place on every team member (d0 is
 // member 0's copy, members pstride apart).  The range goes through a
 // register tile: each lane loads kMcastTile 16-byte vectors once, then the
@@ -953,6 +987,10 @@ __device__ __forceinline__ void multicast(uint8_t *d0, uint64_t pstride, int P, 
                 const uint64_t o = (q & 1) ? len - 16 : 0;
                 st_any<NT, v4u>(d0 + (q >> 1) * pstride + o, ld_any<true, v4u>(src + o));
             }
+    if (nv <= kMcastTile / 4 * bd && P <= 16) {
+        if (nv) mcast_small<NT, kMcastTile / 4>(d0 + head, pstride, P, src + head, (uint32_t)nv, worker);
+        return;
+    }
     for (uint64_t i0 = threadIdx.x; i0 < nv; i0 += (uint64_t)kMcastTile * bd) {
         const uint8_t *s = src + head + 16 * i0;
         v4u r[kMcastTile];
