@@ -56,12 +56,14 @@ __device__ __forceinline__ void stamp(uint64_t *stamps, uint64_t idx)
 // Tasks of a launch's first phases, staged in LDS: a work-group's first task
 // of each phase and that task's descriptors (a wavefront pack's, or a byte
 // range's one; a thread pack's lanes read their own).
-constexpr int kStagePhases = 16, kStageDescs = 16;
+// kStageDescs is four wavefronts' worth for 16 phases: at 5 KB the stage does
+// not limit how many small work-groups a CU holds.
+constexpr int kStagePhases = 16, kStageDescs = 64;
 struct PlanStage {
     uint32_t first[kStagePhases + 1];   // task offsets of the phases
     uint32_t pad[3];
     PlanTask task[kStagePhases];
-    shmemx_desc_t desc[kStagePhases][kStageDescs];
+    shmemx_desc_t desc[kStageDescs];    // per phase as many as the work-group has wavefronts
 };
 
 // `staged`: the task's descriptors in LDS, or null.
@@ -103,8 +105,8 @@ __device__ __forceinline__ void run_task(const shmemx_dctx_pub_t &c, const shmem
 }
 
 // Bound by latency: a phase is its slowest operation's round trips and a
-// grid barrier, which invalidates the caches.  So the first kStagePhases
-// phases' tasks and descriptors are read once, before the first phase, all
+// grid barrier, which invalidates the caches.  So the first phases' tasks
+// (up to kStagePhases) and descriptors are read once, before the first, all
 // phases at a time; read phase by phase they were three dependent round
 // trips to memory behind every barrier.  4-PE program of 8 epochs of 125
 // put/get and 10^4 fetch_add: 42.9 us without, 39.8 with the tasks staged and
@@ -115,7 +117,8 @@ __global__ void __launch_bounds__(1024) k_plan_fused(shmemx_dctx_pub_t c, const 
                                                      int nphases, uint64_t *results, uint64_t *stamps, uint64_t *bar)
 {
     __shared__ PlanStage S;
-    const int ns = min(nphases, kStagePhases);
+    const int waves = (int)blockDim.x / 64;
+    const int ns = min(nphases, min(kStagePhases, kStageDescs / waves));
     for (int i = threadIdx.x; i <= ns; i += blockDim.x) S.first[i] = phase[i];
     __syncthreads();
     for (int i = threadIdx.x; i < ns * (int)(sizeof(PlanTask) / 4); i += blockDim.x) {
@@ -124,10 +127,10 @@ __global__ void __launch_bounds__(1024) k_plan_fused(shmemx_dctx_pub_t c, const 
         if (t < S.first[ph + 1]) ((uint32_t *)&S.task[ph])[w] = ((const uint32_t *)(T + t))[w];
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < ns * kStageDescs * 4; i += blockDim.x) {
-        const int ph = i / (kStageDescs * 4), k = i / 4 % kStageDescs;
+    for (int i = threadIdx.x; i < ns * waves * 4; i += blockDim.x) {
+        const int slot = i / 4, ph = slot / waves, k = slot - ph * waves;
         if (S.first[ph] + blockIdx.x < S.first[ph + 1] && S.task[ph].kind != TK_THREAD && k < (int)S.task[ph].count)
-            ((vshmem_detail::v4u *)&S.desc[ph][k])[i % 4] = ((const vshmem_detail::v4u *)(D + S.task[ph].first + k))[i % 4];
+            ((vshmem_detail::v4u *)&S.desc[slot])[i % 4] = ((const vshmem_detail::v4u *)(D + S.task[ph].first + k))[i % 4];
     }
     __syncthreads();
     uint64_t g = kNoBarrierYet;
@@ -151,7 +154,7 @@ __global__ void __launch_bounds__(1024) k_plan_fused(shmemx_dctx_pub_t c, const 
 #pragma unroll
                 for (int i = 0; i < (int)(sizeof(PlanTask) / 4); ++i) w[i] = __builtin_amdgcn_readfirstlane(q[i]);
             }
-            run_task(c, D, task, staged ? S.desc[ph] : nullptr, results, stamps);
+            run_task(c, D, task, staged ? S.desc + ph * waves : nullptr, results, stamps);
         }
         // Ordering point: every work-group's earlier operations complete
         // before any later operation starts.
