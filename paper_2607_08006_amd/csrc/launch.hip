@@ -38,6 +38,7 @@ constexpr int kIndexItems = 8;              // descriptors per index thread per 
 constexpr uint32_t kLdsEpochs = 4096;       // epochs whose counters the index kernel keeps in LDS
 constexpr uint32_t kLdsBuckets = 8192;      // buckets whose counters the index kernel keeps in LDS
 constexpr uint32_t kExecLdsPhases = 512;    // phases whose bounds the executor keeps in LDS
+constexpr uint32_t kStageDescs = 64;        // descriptors the executor stages in LDS
 constexpr uint32_t kIndexTile = kIndexThreads * kIndexItems;
 static_assert(kIndexThreads <= (1 << 19) && kIndexMaxPes <= (1 << 12), "sync_entry packs 19 + 1 + 12 bits");
 constexpr uint64_t kMaxTable = 1ull << 26;  // descriptors per table
@@ -780,6 +781,13 @@ __device__ __forceinline__ uint32_t wave_search(const uint64_t *cs, uint32_t lo,
 }
 
 // Executor: up to exec_grid work-groups; those past ctl->active leave.
+//
+// Bound by latency, as the plans' kernel is: a phase is its slowest
+// operation's round trips and a grid barrier that invalidates the caches.
+// Phase bounds, and of the first phases (up to kStageDescs descriptors) the
+// work-group's first task where that is a wavefront pack, are therefore read
+// once, before the first phase.  4-PE mixed program: this kernel took 51.6 us
+// and takes 40.3.
 __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
 {
     __shared__ shmemx_tune_t tune;
@@ -788,21 +796,33 @@ __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
     // dependent memory round trips in every work-group.
     __shared__ uint32_t s_off[3 * kExecLdsPhases + 1];
     __shared__ uint64_t s_c0[kExecLdsPhases], s_c1[kExecLdsPhases];
+    __shared__ __align__(16) shmemx_desc_t s_desc[kStageDescs];
     const Ws &w = a.w;
     const uint32_t active = rfl(w.ctl->active), last = rfl(w.ctl->last);
     if (blockIdx.x >= active) return;
     if (threadIdx.x == 0) tune = *a.tune;
     const bool lds = last <= kExecLdsPhases;
+    const uint32_t bd = blockDim.x, waves = bd / 64, wave = threadIdx.x / 64;
+    uint32_t staged = 0;   // phases whose first pack is in LDS
     if (lds) {
-        for (uint32_t k = threadIdx.x; k <= 3 * last; k += blockDim.x) s_off[k] = w.off[k];
+        for (uint32_t k = threadIdx.x; k <= 3 * last; k += bd) s_off[k] = w.off[k];
         __syncthreads();
-        for (uint32_t ph = threadIdx.x; ph < last; ph += blockDim.x) {
+        for (uint32_t ph = threadIdx.x; ph < last; ph += bd) {
             s_c0[ph] = w.cs[s_off[3 * ph]];
             s_c1[ph] = w.cs[s_off[3 * ph + 1]];
         }
+        // Task blockIdx.x of a phase without work-group tasks is wavefront
+        // pack blockIdx.x, if it has that many.
+        staged = min(last, kStageDescs / waves);
+        for (uint32_t i = threadIdx.x; i < staged * waves * 4; i += bd) {
+            const uint32_t slot = i / 4, ph = slot / waves, k = slot - ph * waves;
+            const uint64_t pos = s_off[3 * ph + 1] + (uint64_t)blockIdx.x * waves + k;
+            if (pos < s_off[3 * ph + 2])
+                ((vshmem_detail::v4u *)(s_desc + slot))[i % 4] = ((const vshmem_detail::v4u *)(a.D + w.sorted[pos]))[i % 4];
+        }
     }
     __syncthreads();
-    const uint32_t bd = blockDim.x, waves = bd / 64;
+    uint64_t g = 0;   // the index kernel cleared the barrier's words
     for (uint32_t ph = 0; ph < last; ++ph) {
         const uint32_t *off = lds ? s_off : w.off;
         const uint32_t o0 = rfl(off[3 * ph]), o1 = rfl(off[3 * ph + 1]);
@@ -826,19 +846,19 @@ __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
                 const uint64_t hi = lo + ch < d.nbytes ? lo + ch : d.nbytes;
                 exec_wg(a.c, d, lo, hi, a.results);
             } else if (t < nwg + nwv) {
-                const uint64_t first = o1 + (t - nwg) * waves + threadIdx.x / 64;
-                if (first < o2) exec_wave(a.c, load_desc(a.D + w.sorted[first]), a.results);
+                const uint64_t first = o1 + (t - nwg) * waves + wave;
+                if (first < o2) {
+                    shmemx_desc_t d;
+                    if (ph < staged && nwg == 0 && t == blockIdx.x) d = s_desc[ph * waves + wave];
+                    else d = load_desc(a.D + w.sorted[first]);
+                    exec_wave(a.c, d, a.results);
+                }
             } else {
                 const uint64_t idx = o2 + (t - nwg - nwv) * bd + threadIdx.x;
-                if (idx < o3) exec_thread(a.c, load_desc(a.D + w.sorted[idx]), a.results);
+                if (idx < o3) exec_lanes(a.c, load_desc(a.D + w.sorted[idx]), a.results);
             }
         }
-        if (ph + 1 < last) {
-            vshmem_detail::wait_vm_complete();
-            __syncthreads();
-            if (threadIdx.x == 0) vshmem_detail::counter_barrier(a.c, w.bar, active);
-            __syncthreads();
-        }
+        if (ph + 1 < last) phase_barrier(a.c, w.bar, active, g);
     }
     vshmem_detail::release_wg_at_exit();   // quiet
 }
