@@ -2,13 +2,15 @@
 // read on the device at every launch, so a kernel (or a copy) may rewrite it
 // between launches; the host never sees its contents.
 //
-// The fused form runs three kernels on the caller's stream and together they
+// The fused form runs four kernels on the caller's stream and together they
 // derive what the host plan builder derives.  The classify kernel (one
 // thread per descriptor) validates each operation and resolves its scope and
-// chunking from the tune table; the index kernel (one work-group) finds each
-// operation's phase from its issuer's ordering points (barriers seen, fences
-// and quiets since the last barrier) and counting-sorts the operations by
-// (phase, kind).  The executor then runs the phases in order; inside a
+// chunking from the tune table; the index kernel (a work-group per 1024
+// descriptors, or one alone: see kParTable) finds each operation's phase from
+// its issuer's ordering points (barriers seen, fences and quiets since the
+// last barrier) and counts the operations by (phase, kind); the scatter kernel
+// (not run when one work-group indexes) writes them in that order.  The
+// executor then runs the phases in order; inside a
 // phase the tasks (work-group byte ranges first, then wavefront packs, then
 // single-lane packs) are dealt to its work-groups round robin, and a grid
 // barrier separates the phases.
@@ -32,7 +34,7 @@ namespace {
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr int kIndexThreads = 1024;
 constexpr int kIndexWaves = kIndexThreads / 64;
-constexpr int kClassifyThreads = 256;
+constexpr int kClassifyThreads = 1024;      // one tile of the parallel index
 constexpr int kIndexMaxPes = 4096;          // per-issuer ordering state held in LDS
 constexpr int kIndexItems = 8;              // descriptors per index thread per tile
 constexpr uint32_t kLdsEpochs = 4096;       // epochs whose counters the index kernel keeps in LDS
@@ -40,6 +42,16 @@ constexpr uint32_t kLdsBuckets = 8192;      // buckets whose counters the index 
 constexpr uint32_t kExecLdsPhases = 512;    // phases whose bounds the executor keeps in LDS
 constexpr uint32_t kStageDescs = 64;        // descriptors the executor stages in LDS
 constexpr uint32_t kIndexTile = kIndexThreads * kIndexItems;
+// The index of tables of up to kParTable descriptors is built by one
+// work-group per kParTile of them, when the table has at most kParSync
+// ordering points and no operation of kParTasks or more work-group tasks (so
+// that 32 bits hold any sum of tasks).  Otherwise one work-group builds it.
+constexpr uint32_t kParTile = kIndexThreads;
+constexpr uint32_t kParTable = 65536, kParTiles = kParTable / kParTile;
+constexpr uint32_t kParSync = 1024;
+constexpr uint32_t kParTasks = 65536;
+constexpr uint32_t kParBuckets = 8192;      // counters (packed count and tasks) in LDS and in memory
+constexpr uint32_t kParWords = 64;          // sub-buckets of a phase's single-lane operations, by word
 static_assert(kIndexThreads <= (1 << 19) && kIndexMaxPes <= (1 << 12), "sync_entry packs 19 + 1 + 12 bits");
 constexpr uint64_t kMaxTable = 1ull << 26;  // descriptors per table
 
@@ -49,7 +61,9 @@ struct Ctl {
     uint32_t active;   // executor work-groups that take part (the rest leave at once)
     uint32_t last;     // 1 + the last phase that has tasks (0: nothing to run)
     uint32_t nvalid;   // operations that execute
-    uint32_t pad[12];
+    uint32_t par;      // 1: keys, ranks and counters of the parallel index wait for k_batch_scatter
+    uint32_t done;     // index work-groups that have added their counts
+    uint32_t pad[10];
 };
 
 // Sections of a workspace for tables of up to `cap` descriptors.  The
@@ -68,7 +82,9 @@ struct Ws {
     uint32_t *cnt;     // per bucket: count, then scatter cursor
     uint32_t *off;     // per bucket: first sorted position (one extra entry: the end)
     uint64_t *cs;      // per sorted position: first work-group task (one extra entry)
+    uint64_t *par;     // kParBuckets counters of the parallel index: operations << 32 | work-group tasks
 };
+constexpr uint64_t kParBytes = kParBuckets * 8;
 
 constexpr uint64_t kHeaderBytes = VSHMEM_SYNC_GEN_OFF + 256;
 
@@ -128,6 +144,7 @@ Ws ws_carve(uint8_t *w, uint64_t cap)
         *dst[i] = p;
         p += align256(s[i]);
     }
+    r.par = (uint64_t *)p;   // after the sections: allocations add kParBytes to ws_bytes(cap)
     return r;
 }
 
@@ -137,7 +154,7 @@ struct BatchArgs {
     uint32_t n;
     uint32_t exec_wg;    // executor work-group size
     uint32_t exec_grid;  // executor grid
-    uint32_t pad;
+    uint32_t tiles;      // kParTile descriptors each; 0: more than kParTable descriptors
     const shmemx_tune_t *tune;
     uint64_t *results;
     Ws w;
@@ -166,6 +183,9 @@ __device__ __forceinline__ bool dev_valid(const shmemx_dctx_pub_t &c, const shme
     if (d.op == SHMEMX_OP_PUT_SIGNAL && ((d.cond & 7) || !dev_in_heap(c, d.cond, 8))) return false;
     return true;
 }
+
+__device__ __forceinline__ uint32_t rfl(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint64_t rfl64(uint64_t x) { return vshmem_detail::first_lane64(x); }
 
 __device__ __forceinline__ bool is_data_op(uint8_t op)
 {
@@ -327,17 +347,19 @@ __device__ __forceinline__ void agg_inc(uint32_t *counter, const uint32_t (&key)
 }
 
 // Class word of a descriptor, written by the classify kernel: issuer in
-// bits 0-11, type in bits 12-13, kind in bits 14-15.
+// bits 0-11, type in bits 12-13, kind in bits 14-15, and for single-lane
+// atomics a hash of the word in bits 16-21.
 constexpr uint32_t kTypeSkip = 0;      // NOP or invalid: not executed
 constexpr uint32_t kTypeFence = 1;     // fence or quiet
 constexpr uint32_t kTypeBarrier = 2;   // barrier_all
 constexpr uint32_t kTypeData = 3;      // executes
-__device__ __forceinline__ uint32_t class_word(uint32_t iss, uint32_t type, uint32_t kind)
+__device__ __forceinline__ uint32_t class_word(uint32_t iss, uint32_t type, uint32_t kind, uint32_t hash)
 {
-    return iss | (type << 12) | (kind << 14);
+    return iss | (type << 12) | (kind << 14) | (hash << 16);
 }
 __device__ __forceinline__ uint32_t class_type(uint32_t cw) { return (cw >> 12) & 3u; }
-__device__ __forceinline__ uint32_t class_kind(uint32_t cw) { return cw >> 14; }
+__device__ __forceinline__ uint32_t class_kind(uint32_t cw) { return (cw >> 14) & 3u; }
+__device__ __forceinline__ uint32_t class_hash(uint32_t cw) { return cw >> 16; }
 __device__ __forceinline__ uint32_t class_issuer(uint32_t cw) { return cw & 0xFFFu; }
 
 // One entry of a tile's list of ordering points: tile position, barrier
@@ -386,54 +408,98 @@ __device__ __forceinline__ void store_run(uint32_t *p, uint32_t i0, uint32_t n, 
 // Classify kernel: one thread per descriptor, over the whole GPU.  It
 // validates the descriptor, resolves its scope and chunking, and writes its
 // class word (to the key section) and its work-group task count.  Invalid
-// descriptors latch SHMEMX_DEVERR_BAD_DESC and are skipped.
+// descriptors latch SHMEMX_DEVERR_BAD_DESC and are skipped.  Each work-group
+// (one tile) also lists its ordering points in table order (to the eb
+// section, count and a flag for operations of too many tasks to the maxf
+// section), and the counters of the parallel index are cleared.
 __global__ void __launch_bounds__(kClassifyThreads) k_batch_classify(BatchArgs a)
 {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.n) return;
-    const shmemx_desc_t d = load_desc_head(a.D + i);
-    const uint32_t iss = (uint32_t)d.issuer_pe;
-    const bool iss_ok = iss < (uint32_t)a.c.npes;
-    uint32_t type = kTypeSkip, kind = 0, nch = 0;
-    if (iss_ok && is_sync_op(d.op)) {
-        type = d.op == SHMEMX_OP_BARRIER_ALL ? kTypeBarrier : kTypeFence;
-    } else if (iss_ok && is_data_op(d.op) && dev_valid(a.c, d, a.n, a.results)) {
-        const shmemx_tune_t &tune = *a.tune;
-        const int sc = resolve_scope(d, tune);
-        kind = sc == SHMEMX_SCOPE_THREAD ? 2u : (sc == SHMEMX_SCOPE_WAVE ? 1u : 0u);
-        if (kind == 0) {
-            const uint64_t ch = resolve_chunk(d, sc, tune);
-            const uint64_t k = d.nbytes ? (d.nbytes + ch - 1) / ch : 1;
-            nch = k < 0xFFFFFFFFull ? (uint32_t)k : 0xFFFFFFFFu;
-        }
-        type = kTypeData;
-    } else if (d.op != SHMEMX_OP_NOP) {
-        // A bad code, WAIT_UNTIL, a bad issuer or an invalid operation.
-        vshmem_detail::latch_error(a.c, SHMEMX_DEVERR_BAD_DESC);
+    __shared__ uint32_t wcount[kClassifyThreads / 64];
+    __shared__ uint32_t s_big;
+    const uint32_t i = blockIdx.x * kClassifyThreads + threadIdx.x;
+    if (threadIdx.x == 0) s_big = 0;
+    if (a.tiles) {
+        for (uint32_t k = i; k < kParBuckets; k += gridDim.x * kClassifyThreads) a.w.par[k] = 0;
+        if (i == 0) a.w.ctl->done = 0;
     }
-    a.w.key[i] = class_word(iss_ok ? iss : 0, type, kind);
-    a.w.nch[i] = nch;
+    uint32_t type = kTypeSkip, kind = 0, nch = 0, hash = 0, iss = 0;
+    if (i < a.n) {
+        const shmemx_desc_t d = load_desc_head(a.D + i);
+        iss = (uint32_t)d.issuer_pe;
+        const bool iss_ok = iss < (uint32_t)a.c.npes;
+        if (!iss_ok) iss = 0;
+        if (iss_ok && is_sync_op(d.op)) {
+            type = d.op == SHMEMX_OP_BARRIER_ALL ? kTypeBarrier : kTypeFence;
+        } else if (iss_ok && is_data_op(d.op) && dev_valid(a.c, d, a.n, a.results)) {
+            const shmemx_tune_t &tune = *a.tune;
+            const int sc = resolve_scope(d, tune);
+            kind = sc == SHMEMX_SCOPE_THREAD ? 2u : (sc == SHMEMX_SCOPE_WAVE ? 1u : 0u);
+            if (kind == 0) {
+                const uint64_t ch = resolve_chunk(d, sc, tune);
+                const uint64_t k = d.nbytes ? (d.nbytes + ch - 1) / ch : 1;
+                nch = k < 0xFFFFFFFFull ? (uint32_t)k : 0xFFFFFFFFu;
+            }
+            // Single-lane atomics of one word share a sub-bucket, so that
+            // they meet in a wavefront and combine.
+            if (kind == 2 && is_amo_op(d.op))
+                hash = (((uint32_t)(d.src >> 3) + 13u * (uint32_t)d.target_pe) * 0x9E3779B1u) >> 26;
+            type = kTypeData;
+        } else if (d.op != SHMEMX_OP_NOP) {
+            // A bad code, WAIT_UNTIL, a bad issuer or an invalid operation.
+            vshmem_detail::latch_error(a.c, SHMEMX_DEVERR_BAD_DESC);
+        }
+        a.w.key[i] = class_word(iss, type, kind, hash);
+        a.w.nch[i] = nch;
+    }
+    if (!a.tiles) return;
+    const bool sync = type == kTypeFence || type == kTypeBarrier;
+    const uint64_t m = __ballot(sync);
+    const uint32_t wave = threadIdx.x / 64, lane = __lane_id();
+    if (lane == 0) wcount[wave] = (uint32_t)__builtin_popcountll(m);
+    __syncthreads();
+    if (nch >= kParTasks) s_big = 1;   // every writer stores the same value
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < kClassifyThreads / 64; ++k) {
+        before += k < wave ? wcount[k] : 0;
+        all += wcount[k];
+    }
+    // sync_entry's position is the one inside the tile.
+    if (sync)
+        a.w.eb[blockIdx.x * kClassifyThreads + before + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] =
+            sync_entry(threadIdx.x, type == kTypeBarrier, iss);
+    __syncthreads();
+    if (threadIdx.x == 0) a.w.maxf[blockIdx.x] = all | (s_big << 31);
 }
 
-// Index kernel: one work-group of kIndexThreads threads, after the classify
-// kernel.  It walks the table in tiles of kIndexTile positions and loads a
-// tile's words before it uses them, so one work-group pays one memory
-// latency per tile and pass.  Past pass 1, thread t takes the run of
-// kIndexItems consecutive positions starting at t * kIndexItems: it reads
-// and writes its per-descriptor words as 16-byte vectors, and a tile needs
-// one work-group scan of per-thread sums.  The per-epoch and per-bucket
-// counters live in LDS while they fit (the usual case), so the counting
-// sort runs on LDS atomics.
-__global__ void __launch_bounds__(kIndexThreads) k_batch_index(BatchArgs a)
+// The index of any table, by one work-group of kIndexThreads threads.  It
+// walks the table in tiles of kIndexTile positions and loads a tile's words
+// before it uses them, so one work-group pays one memory latency per tile and
+// pass.  Past pass 1, thread t takes the run of kIndexItems consecutive
+// positions starting at t * kIndexItems: it reads and writes its
+// per-descriptor words as 16-byte vectors, and a tile needs one work-group
+// scan of per-thread sums.  The per-epoch and per-bucket counters live in LDS
+// while they fit (the usual case), so the counting sort runs on LDS atomics.
+struct SerialLds {
+    uint32_t nbar[kIndexMaxPes], nfen[kIndexMaxPes];
+    uint32_t lsync[kIndexThreads];
+    __align__(16) uint32_t wcount[2][kIndexWaves];
+    uint32_t s_tmask[4];
+    uint32_t lepoch[kLdsEpochs];    // per epoch: largest fence count, then first phase
+    uint32_t lcnt[kLdsBuckets];     // per bucket: count, then scatter cursor
+    uint32_t s_max, s_last, s_bad, s_wg;
+};
+__device__ __forceinline__ void index_serial(const BatchArgs &a, SerialLds &L)
 {
     constexpr int R = kIndexItems;
-    __shared__ uint32_t nbar[kIndexMaxPes], nfen[kIndexMaxPes];
-    __shared__ uint32_t lsync[kIndexThreads];
-    __shared__ __align__(16) uint32_t wcount[2][kIndexWaves];
-    __shared__ uint32_t s_tmask[3];
-    __shared__ uint32_t lepoch[kLdsEpochs];    // per epoch: largest fence count, then first phase
-    __shared__ uint32_t lcnt[kLdsBuckets];     // per bucket: count, then scatter cursor
-    __shared__ uint32_t s_max, s_last, s_bad, s_wg;
+    auto &nbar = L.nbar;
+    auto &nfen = L.nfen;
+    auto &lsync = L.lsync;
+    auto &wcount = L.wcount;
+    auto &s_tmask = L.s_tmask;
+    auto &lepoch = L.lepoch;
+    auto &lcnt = L.lcnt;
+    uint32_t &s_max = L.s_max, &s_last = L.s_last, &s_bad = L.s_bad, &s_wg = L.s_wg;
     const uint32_t tid = threadIdx.x, nt = blockDim.x, n = a.n;
     const int npes = a.c.npes;
     const Ws &w = a.w;
@@ -590,6 +656,7 @@ __global__ void __launch_bounds__(kIndexThreads) k_batch_index(BatchArgs a)
             w.ctl->active = 0;
             w.ctl->last = 0;
             w.ctl->nvalid = 0;
+            w.ctl->par = 0;
         }
         return;
     }
@@ -753,13 +820,245 @@ __global__ void __launch_bounds__(kIndexThreads) k_batch_index(BatchArgs a)
         w.ctl->active = s_max == 0 ? 0 : (s_max < a.exec_grid ? s_max : a.exec_grid);
         w.ctl->last = s_last;
         w.ctl->nvalid = nvalid;
+        w.ctl->par = 0;
         w.bar[0] = 0;
         *(uint64_t *)((uint8_t *)w.bar + VSHMEM_SYNC_GEN_OFF) = 0;
     }
 }
 
-__device__ __forceinline__ uint32_t rfl(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ uint64_t rfl64(uint64_t x) { return vshmem_detail::first_lane64(x); }
+// The index of a table of up to kParTable descriptors, by one work-group per
+// tile.  Every work-group reads the whole table's list of ordering points
+// (short: at most kParSync) and derives from it what the serial form derives
+// by walking the table: an operation's barrier epoch and fence count are those
+// after its issuer's last point before it, and the phases of an epoch are one
+// more than the most fences of any issuer in it (phases that hold no operation
+// are skipped by the executor).  An operation's bucket is known then; its rank
+// inside the bucket, and for work-group operations its first task, come from
+// packed counters: one LDS atomic per operation, one atomic in memory per
+// bucket and tile.  The last work-group to add its counts turns them into
+// offsets; k_batch_scatter then writes the sorted order.
+//
+// The serial form is bound by one work-group's latency, 3 ns per descriptor,
+// this one by its chain of dependent steps.  4-PE mixed program (11044
+// descriptors): 36.0 us serial; 12.2 us here and 4.7 us in the scatter kernel,
+// and the whole launch 79.0 -> 58.9 us.  Launches of 300, 16000 and 60000 small
+// puts with 64 barriers between 4 PEs: 82.9 -> 62.6, 155 -> 99, 241 -> 106 us.
+// The dearest points are fences of PEs that seldom issue one (each operation
+// searches far back): 4000 puts, 1000 fences, 64 PEs take 183 us, 179 before.
+struct ParLds {
+    uint64_t cnt[kParBuckets];          // operations << 32 | work-group tasks, of this tile; then before it
+    __align__(16) uint32_t point[kParSync];   // table position << 13 | barrier << 12 | issuer; read four at a time
+    uint32_t epoch[kParSync + 1];       // per point: epoch after it; fences after it in the high half
+    uint32_t base[kParSync + 2];        // per epoch: most fences, then first phase
+    uint32_t nbar[kIndexMaxPes];
+    uint32_t first[kParTiles + 1];      // per tile: its first point
+    uint32_t s_bad, s_big, s_last, s_max, s_lastph;
+};
+
+// cw, nch: this thread's class word and task count, read ahead.
+__device__ __forceinline__ void index_parallel(const BatchArgs &a, ParLds &L, uint32_t cw, uint32_t nch)
+{
+    const uint32_t tid = threadIdx.x, n = a.n, npts = L.first[a.tiles];
+    const Ws &w = a.w;
+    for (int p = tid; p < a.c.npes; p += kIndexThreads) L.nbar[p] = 0;
+    for (uint32_t e = tid; e < kParSync + 2; e += kIndexThreads) L.base[e] = 0;
+    for (uint32_t t = tid / 64; t < a.tiles; t += kIndexWaves)
+        for (uint32_t k = __lane_id(); k < L.first[t + 1] - L.first[t]; k += 64)
+            L.point[L.first[t] + k] = w.eb[t * kParTile + k] + ((t * kParTile) << 13);
+    if (tid == 0) L.s_bad = L.s_max = L.s_lastph = 0;
+    __syncthreads();
+    // The state after each point (a point per thread).
+    uint32_t eb = 0, ef = 0;
+    if (tid < npts) {
+        const uint32_t me = L.point[tid] & 0xFFFu;
+        for (uint32_t j = 0; j <= tid; j += 4) {
+            const vshmem_detail::v4u q = *(const vshmem_detail::v4u *)(L.point + j);
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t e = q[k];
+                if (j + k <= tid && (e & 0xFFFu) == me) {
+                    const bool bar = (e >> 12) & 1u;
+                    eb = bar ? eb + 1 : eb;
+                    ef = bar ? 0 : ef + 1;
+                }
+            }
+        }
+        L.epoch[tid] = eb | (ef << 16);
+        if (ef) atomicMax(&L.base[eb], ef);
+        if ((L.point[tid] >> 12) & 1u) atomicAdd(&L.nbar[me], 1u);
+    }
+    __syncthreads();
+    // Every PE's program holds the same number of barriers.
+    for (int p = tid; p < a.c.npes; p += kIndexThreads)
+        if (L.nbar[p] != L.nbar[0]) L.s_bad = 1;
+    __syncthreads();
+    if (L.s_bad) {
+        if (blockIdx.x == 0 && tid == 0) {
+            vshmem_detail::latch_error(a.c, SHMEMX_DEVERR_BAD_DESC);
+            w.ctl->nphases = 0;
+            w.ctl->active = 0;
+            w.ctl->last = 0;
+            w.ctl->nvalid = 0;
+            w.ctl->par = 0;
+        }
+        return;
+    }
+    // First phase of each epoch: one epoch per thread, and the last one.
+    const uint32_t nepochs = L.nbar[0] + 1;   // at most kParSync + 1
+    const uint32_t v = tid < nepochs ? L.base[tid] + 1 : 0, tail = nepochs > kIndexThreads ? L.base[kIndexThreads] + 1 : 0;
+    uint32_t nphases = 0;
+    const uint32_t ex = block_scan<kIndexWaves, uint32_t>(v, &nphases);
+    if (tid < nepochs) L.base[tid] = ex;
+    if (tid == 0 && nepochs > kIndexThreads) L.base[kIndexThreads] = nphases;
+    nphases += tail;
+    // Buckets of a phase: work-group, wavefront, then single-lane operations
+    // in kParWords sub-buckets (one when there are many phases).
+    const uint32_t H = nphases * (2 + kParWords) <= kParBuckets ? kParWords : 1;
+    const uint32_t per = 2 + H, nbk = nphases * per;   // 3 * (2 kParSync + 1) fit
+    for (uint32_t k = tid; k < nbk; k += kIndexThreads) L.cnt[k] = 0;
+    __syncthreads();
+    const uint32_t i = blockIdx.x * kParTile + tid;
+    const bool live = class_type(cw) == kTypeData;
+    uint32_t key = kNone;
+    uint64_t r = 0;
+    if (live) {
+        // Its issuer's last point before it, from the tile's last point back.
+        const uint32_t end = L.first[blockIdx.x + 1];
+        uint32_t at = kNone;
+        for (uint32_t j = (end + 3) / 4; j > 0 && at == kNone; --j) {
+            const vshmem_detail::v4u q = *(const vshmem_detail::v4u *)(L.point + 4 * (j - 1));
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint32_t pt = q[k], m = 4 * (j - 1) + k;
+                if (m < end && (pt & 0xFFFu) == class_issuer(cw) && (pt >> 13) < i) at = m;
+            }
+        }
+        const uint32_t e = at == kNone ? 0 : L.epoch[at] & 0xFFFFu, f = at == kNone ? 0 : L.epoch[at] >> 16;
+        const uint32_t kind = class_kind(cw);
+        key = (L.base[e] + f) * per + (kind < 2 ? kind : 2 + (class_hash(cw) & (H - 1)));
+        r = atomicAdd((unsigned long long *)&L.cnt[key], (1ull << 32) | nch);
+    }
+    __syncthreads();
+    for (uint32_t k = tid; k < nbk; k += kIndexThreads)
+        if (L.cnt[k])
+            L.cnt[k] = __hip_atomic_fetch_add(w.par + k, L.cnt[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();   // every thread's atomics have returned: the tile's counts are in
+    if (i < n) {
+        w.key[i] = key;
+        if (live) {
+            const uint64_t q = L.cnt[key] + r;
+            w.ef[i] = (uint32_t)(q >> 32);   // rank in the bucket
+            w.nch[i] = (uint32_t)q;          // tasks before it in the bucket
+        }
+    }
+    if (tid == 0)
+        L.s_last = __hip_atomic_fetch_add(&w.ctl->done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == a.tiles - 1;
+    __syncthreads();
+    if (!L.s_last) return;
+
+    // Offsets.  The counters were built with atomics, performed in memory:
+    // they are read the same way.
+    uint64_t carry = 0;
+    for (uint32_t k0 = 0; k0 < nbk; k0 += kIndexThreads) {
+        const uint32_t k = k0 + tid;
+        const uint64_t c = k < nbk ? __hip_atomic_load(w.par + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        uint64_t tot = 0;
+        const uint64_t before = carry + block_scan<kIndexWaves, uint64_t>(c, &tot);
+        carry += tot;
+        if (k < nbk) {
+            w.par[k] = before;
+            L.cnt[k] = before;
+            const uint32_t ph = k / per, b = k - ph * per;
+            if (b <= 2) w.off[3 * ph + b] = (uint32_t)(before >> 32);
+        }
+    }
+    const uint32_t nvalid = (uint32_t)(carry >> 32);
+    if (tid == 0) {
+        w.off[3 * nphases] = nvalid;
+        w.cs[nvalid] = (uint32_t)carry;
+    }
+    __syncthreads();
+    // Tasks per phase, the executor's active work-groups and the last phase
+    // with tasks.
+    const uint32_t bd = a.exec_wg, waves = bd / 64;
+    for (uint32_t ph = tid; ph < nphases; ph += kIndexThreads) {
+        const uint64_t q0 = L.cnt[ph * per], q1 = L.cnt[ph * per + 1], q2 = L.cnt[ph * per + 2];
+        const uint64_t q3 = ph + 1 < nphases ? L.cnt[(ph + 1) * per] : carry;
+        const uint32_t o1 = (uint32_t)(q1 >> 32), o2 = (uint32_t)(q2 >> 32), o3 = (uint32_t)(q3 >> 32);
+        const uint64_t nt_ph = (uint64_t)((uint32_t)q1 - (uint32_t)q0) + (o2 - o1 + waves - 1) / waves + (o3 - o2 + bd - 1) / bd;
+        if (nt_ph) {
+            atomicMax(&L.s_max, nt_ph < 0xFFFFFFFFull ? (uint32_t)nt_ph : 0xFFFFFFFFu);
+            atomicMax(&L.s_lastph, ph + 1);
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        w.ctl->nphases = nphases;
+        w.ctl->active = L.s_max == 0 ? 0 : (L.s_max < a.exec_grid ? L.s_max : a.exec_grid);
+        w.ctl->last = L.s_lastph;
+        w.ctl->nvalid = nvalid;
+        w.ctl->par = 1;
+        w.bar[0] = 0;
+        *(uint64_t *)((uint8_t *)w.bar + VSHMEM_SYNC_GEN_OFF) = 0;
+    }
+}
+
+// Index kernel, after the classify kernel: one work-group per tile, or one
+// alone for a table of more than kParTable descriptors.
+__global__ void __launch_bounds__(kIndexThreads) k_batch_index(BatchArgs a)
+{
+    __shared__ __align__(16) union {
+        SerialLds serial;
+        ParLds par;
+    } L;
+    if (a.tiles) {
+        const uint32_t i = blockIdx.x * kParTile + threadIdx.x;
+        const uint32_t cw = i < a.n ? a.w.key[i] : 0, nch = i < a.n ? a.w.nch[i] : 0;
+        // Points per tile, and whether the table qualifies.
+        if (threadIdx.x < 64) {
+            static_assert(kParTiles <= 64, "one lane per tile");
+            const uint32_t t = threadIdx.x, c = t < a.tiles ? a.w.maxf[t] : 0;
+            uint32_t sum = c & 0x7FFFFFFFu;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t y = __shfl_up(sum, o, 64);
+                if ((int)t >= o) sum += y;
+            }
+            if (t < a.tiles) L.par.first[t + 1] = sum;
+            const bool big = __ballot(c >> 31) != 0;
+            if (t == 0) {
+                L.par.first[0] = 0;
+                L.par.s_big = big;
+            }
+        }
+        __syncthreads();
+        if (!rfl(L.par.s_big) && rfl(L.par.first[a.tiles]) <= kParSync) {
+            index_parallel(a, L.par, cw, nch);
+            return;
+        }
+        if (blockIdx.x != 0) return;
+        __syncthreads();   // the serial form reuses the words just read
+    }
+    index_serial(a, L.serial);
+}
+
+// Scatter kernel: the sorted order from the parallel index's keys, ranks and
+// offsets, one descriptor per thread.  The order inside a bucket is free: its
+// operations run concurrently anyway.  Two dependent loads and a store: launch
+// latency bounds it (4.7 us for 11044 descriptors).
+__global__ void __launch_bounds__(256) k_batch_scatter(BatchArgs a)
+{
+    const Ws &w = a.w;
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= a.n) return;
+    // All at once; only ctl->par says whether they are what they should be.
+    const uint32_t key = w.key[i], rank = w.ef[i], tasks = w.nch[i];
+    if (!w.ctl->par || key == kNone) return;
+    const uint64_t q = w.par[key];
+    const uint32_t pos = (uint32_t)(q >> 32) + rank;
+    w.sorted[pos] = i;
+    w.cs[pos] = (uint32_t)q + tasks;
+}
 
 // Last sorted position s in [lo, hi) with cs[s] <= target (cs strictly
 // increasing over work-group operations): a 64-way search by one wavefront.
@@ -807,9 +1106,11 @@ __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
     if (lds) {
         for (uint32_t k = threadIdx.x; k <= 3 * last; k += bd) s_off[k] = w.off[k];
         __syncthreads();
-        for (uint32_t ph = threadIdx.x; ph < last; ph += bd) {
-            s_c0[ph] = w.cs[s_off[3 * ph]];
-            s_c1[ph] = w.cs[s_off[3 * ph + 1]];
+        // (The first bd phases' task bounds are read beside the packs.)
+        uint64_t c0 = 0, c1 = 0;
+        if (threadIdx.x < last) {
+            c0 = w.cs[s_off[3 * threadIdx.x]];
+            c1 = w.cs[s_off[3 * threadIdx.x + 1]];
         }
         // Task blockIdx.x of a phase without work-group tasks is wavefront
         // pack blockIdx.x, if it has that many.
@@ -819,6 +1120,14 @@ __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
             const uint64_t pos = s_off[3 * ph + 1] + (uint64_t)blockIdx.x * waves + k;
             if (pos < s_off[3 * ph + 2])
                 ((vshmem_detail::v4u *)(s_desc + slot))[i % 4] = ((const vshmem_detail::v4u *)(a.D + w.sorted[pos]))[i % 4];
+        }
+        if (threadIdx.x < last) {
+            s_c0[threadIdx.x] = c0;
+            s_c1[threadIdx.x] = c1;
+        }
+        for (uint32_t ph = threadIdx.x + bd; ph < last; ph += bd) {
+            s_c0[ph] = w.cs[s_off[3 * ph]];
+            s_c1[ph] = w.cs[s_off[3 * ph + 1]];
         }
     }
     __syncthreads();
@@ -950,8 +1259,10 @@ int launch_fused(const shmemx_desc_t *d_descs, size_t n, uint64_t *d_results, co
     a.results = d_results;
     a.w = ws_carve(ws, cap);
     const uint32_t ncls = (uint32_t)((n + kClassifyThreads - 1) / kClassifyThreads);
+    a.tiles = n <= kParTable ? ncls : 0;
     hipLaunchKernelGGL(k_batch_classify, dim3(ncls), dim3(kClassifyThreads), 0, stream, a);
-    hipLaunchKernelGGL(k_batch_index, dim3(1), dim3(kIndexThreads), 0, stream, a);
+    hipLaunchKernelGGL(k_batch_index, dim3(a.tiles ? a.tiles : 1), dim3(kIndexThreads), 0, stream, a);
+    if (a.tiles) hipLaunchKernelGGL(k_batch_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(k_batch_exec, dim3(grid), dim3(wg), 0, stream, a);
     VSHMEM_HIP(hipGetLastError());
     return SHMEMX_OK;
@@ -981,7 +1292,7 @@ std::map<int, uint8_t *> g_noalloc_ptr;     // device ordinal -> address of its 
 // that every call on a device shares.  Its device address comes from
 // hipGetSymbolAddress once per device; in host code the name is only a
 // stand-in, never an address to hand to a kernel.
-static __device__ __align__(256) uint8_t scratch[kNoAllocBytes];
+static __device__ __align__(256) uint8_t scratch[kNoAllocBytes + kParBytes];
 
 struct shmemx_graph {
     hipGraph_t graph = nullptr;
@@ -1029,7 +1340,7 @@ int shmemx_launch_batch(const shmemx_desc_t *d_descs, size_t n, uint64_t *d_resu
             sw.buf = nullptr;
             sw.cap = 0;
             const uint64_t want = std::max<uint64_t>(n, 4096);
-            VSHMEM_HIP(hipMalloc((void **)&sw.buf, ws_bytes(want)));
+            VSHMEM_HIP(hipMalloc((void **)&sw.buf, ws_bytes(want) + kParBytes));
             sw.cap = want;
         }
         buf = sw.buf;
@@ -1077,7 +1388,7 @@ int shmemx_graph_build(const shmemx_desc_t *d_descs, size_t n, uint64_t *d_resul
     auto *g = new shmemx_graph();
     int rc = SHMEMX_OK;
     const uint64_t cap = std::max<uint64_t>(n, 1);
-    if (form == 1 && VSHMEM_HIP_FAILED(hipMalloc((void **)&g->ws, ws_bytes(cap)))) rc = SHMEMX_ERR_HIP;
+    if (form == 1 && VSHMEM_HIP_FAILED(hipMalloc((void **)&g->ws, ws_bytes(cap) + kParBytes))) rc = SHMEMX_ERR_HIP;
     hipStream_t cs = nullptr;
     if (!rc && VSHMEM_HIP_FAILED(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking))) rc = SHMEMX_ERR_HIP;
     if (!rc && VSHMEM_HIP_FAILED(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal))) rc = SHMEMX_ERR_HIP;

@@ -94,3 +94,74 @@ def test_contended_adds_and_xors(form, nwords):
                 cur = (cur ^ nxt[cur]) if xor else (cur + nxt[cur]) & M
             assert cur == int(ref[pe, 8 * w:8 * w + 8].view(np.uint64)[0])
         assert_no_device_errors()
+
+
+@pytest.mark.parametrize("case", ["one_tile", "tile_edge", "points_at_limit", "points_past_limit", "large_table",
+                                  "many_tasks", "unequal_barriers"])
+def test_index_forms(case):
+    """Tables on both sides of what the parallel index takes: whole tiles of
+    1024 descriptors and one more, 1024 ordering points and more, more than
+    65536 descriptors, an operation of 65536 work-group tasks; and a table
+    whose PEs see different numbers of barriers, of which nothing runs."""
+    npes, size = 3, 1 << 21
+    x = W.splitmix64(0x1DE, 0, 4096)
+    recs, ref_ops = [], []
+
+    def sync(op, pe):
+        recs.append((op, W.SCOPE_WG, 0, pe, pe, W.NO_RESULT, 0, 0, 0, 0, 0))
+
+    def put(k, n=24, scope=W.SCOPE_AUTO):   # slot k of the target's second half, from the issuer's first
+        pe = k % npes
+        recs.append((W.OP_PUT, scope, 0, pe, (pe + 1) % npes, W.NO_RESULT, 64 * (k % 8192), size // 2 + 64 * (k % 8192),
+                     n, 0, 0))
+
+    def epoch(count, at=0, fences=0):
+        for k in range(count):
+            put(at + k, 8 + int(x[k % 4096] % np.uint64(56)), (W.SCOPE_AUTO, W.SCOPE_WAVE, W.SCOPE_WG)[k % 3])
+            if fences and k % max(1, count // fences) == 0:
+                sync(W.OP_FENCE, k % npes)
+        for p in range(npes):
+            sync(W.OP_BARRIER_ALL, p)
+
+    if case == "one_tile":
+        epoch(1021)
+    elif case == "tile_edge":
+        epoch(500, fences=7), epoch(520), epoch(1500, fences=3)
+        assert len(recs) > 2048
+    elif case in ("points_at_limit", "points_past_limit"):
+        for e in range(341):
+            epoch(3, at=3 * e)
+        sync(W.OP_FENCE, 0)
+        if case == "points_past_limit":
+            sync(W.OP_QUIET, 1)
+        put(7777)
+    elif case == "large_table":
+        for e in range(9):
+            epoch(8000)
+        assert len(recs) > 65536
+    elif case == "many_tasks":
+        epoch(40)
+        recs.append((W.OP_PUT, W.SCOPE_WG, 0, 0, 1, W.NO_RESULT, 0, size // 2, size // 2, 0, 0))
+    else:
+        epoch(100)
+        sync(W.OP_BARRIER_ALL, 1)
+        put(5)
+    d = W.descs(recs)
+    with heap(npes, size) as v:
+        t = torch()
+        init = W.heap_fill(0x1DE, npes, size)
+        upload(init)
+        table = t.from_numpy(np.ascontiguousarray(d).view(np.uint8).copy()).cuda()
+        tune = v.default_tune()
+        if case == "many_tasks":
+            for c in range(len(tune.chunk)):
+                tune.chunk[c] = 16
+        dt = t.frombuffer(bytearray(bytes(tune)), dtype=t.uint8).cuda()
+        ref = init.copy()
+        if case != "unequal_barriers":
+            oracle.run_program(ref, d)
+        for _ in range(2):
+            v.launch_batch(table, len(d), d_tune=dt)
+            assert np.array_equal(download(size), ref)
+        want = v.DEVERR_BAD_DESC if case == "unequal_barriers" else 0
+        assert v.device_errors() == want
