@@ -468,7 +468,7 @@ int shmemx_barrier_launch(shmem_team_t team, int iters, uint64_t tokens_off, uin
  * SHMEMX_ERR_ARG if team size * wgs_per_pe work-groups cannot be.
  * launch may be NULL; zero fields take the defaults: wgs_per_pe about one
  * work-group per CU in total, work-groups of 1024 threads (256 for the
- * reductions, which accept at most 512; small reductions over 32 to 64
+ * reductions, which accept at most 512; small reductions over 24 to 64
  * members take 512 when the whole shape is left to the library), chunk
  * 256 KiB (reductions 16 KiB), nontemporal copies for alltoall (8 deep) and
  * the reductions.

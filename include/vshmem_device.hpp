@@ -1009,7 +1009,7 @@ __device__ __forceinline__ void multicast(uint8_t *d0, uint64_t pstride, int P, 
 }
 
 // x / d, in 32 bits when both fit (a 64-bit division is a long sequence).
-__device__ __forceinline__ uint64_t udiv(uint64_t x, uint64_t d)
+__host__ __device__ __forceinline__ uint64_t udiv(uint64_t x, uint64_t d)
 {
     return ((x | d) >> 32) == 0 ? (uint32_t)x / (uint32_t)d : x / d;
 }
@@ -1028,15 +1028,22 @@ __device__ __forceinline__ uint64_t udiv(uint64_t x, uint64_t d)
 // fcollect of 300000 bytes 258 us in two rounds, the second a quarter full,
 // and 248 in one.  13 members, 256 MiB: chunks of even size but off the line
 // boundaries 1099 us, on them 759.
+//
+// The launchers compute it on the host: its chain of divisions, and the
+// instructions it brings in, cost each launch 1.4 us (one launch after another,
+// broadcast of 16 bytes over 4 PEs: 4.9 us, and 3.7 from the host, the rate of
+// the launches; of 1 MiB over 64: 16.6 and 14.4).
 struct McastSplit {
     uint64_t chunk, nch;     // bytes per chunk, chunks per range
     uint32_t per, groups;    // members per task, member groups
 };
-__device__ __forceinline__ McastSplit mcast_split(uint64_t n, uint32_t Q, uint32_t P, uint32_t workers, uint64_t chunk)
+__host__ __device__ __forceinline__ uint64_t least(uint64_t a, uint64_t b) { return a < b ? a : b; }
+__host__ __device__ __forceinline__ uint64_t most(uint64_t a, uint64_t b) { return a < b ? b : a; }
+__host__ __device__ __forceinline__ McastSplit mcast_split(uint64_t n, uint32_t Q, uint32_t P, uint32_t workers, uint64_t chunk)
 {
     uint64_t c = chunk, k = udiv(n + c - 1, c);
     if (2 * k * Q < workers) {
-        c = min<uint64_t>(c, 64u << 10);
+        c = least(c, 64u << 10);
         k = udiv(n + c - 1, c);
         for (; c > (16u << 10) && k * Q * P < workers; c >>= 1) k *= 2;
     }
@@ -1044,8 +1051,8 @@ __device__ __forceinline__ McastSplit mcast_split(uint64_t n, uint32_t Q, uint32
     // then as many chunks as fill the last round.
     uint32_t g = 1;
     if (k * Q < workers) {
-        g = min(P, workers / ((uint32_t)k * Q));
-        k = max<uint64_t>(k, workers / (g * Q));
+        g = (uint32_t)least(P, workers / ((uint32_t)k * Q));
+        k = most(k, workers / (g * Q));
     } else {
         k = udiv(udiv(k * Q + workers - 1, workers) * workers, Q);
     }
@@ -1066,9 +1073,8 @@ __device__ __forceinline__ McastSplit mcast_split(uint64_t n, uint32_t Q, uint32
 // 742).
 template <bool NT>
 __device__ __forceinline__ void multicast_all(uint8_t *D, uint64_t ps, uint32_t P, const uint8_t *src, uint64_t sstep,
-                                              uint32_t Q, uint64_t n, const Workers &W, uint64_t chunk)
+                                              uint32_t Q, uint64_t n, const Workers &W, const McastSplit &m)
 {
-    const McastSplit m = mcast_split(n, Q, P, W.n, chunk);
     const uint64_t ntask = m.nch * Q * m.groups;
     for (uint64_t t = W.w; t < ntask; t += W.n) {
         const uint64_t r = udiv(t, m.nch), g = udiv(r, Q), q = r - g * Q;
@@ -1077,17 +1083,6 @@ __device__ __forceinline__ void multicast_all(uint8_t *D, uint64_t ps, uint32_t 
         multicast<NT>(D + p0 * ps + q * n + off, ps, (int)min(m.per, P - p0), src + q * sstep + off,
                       min(m.chunk, n - off), W.w);
     }
-}
-
-// Every member's dest[0, n) <- member root's src[0, n), root included.
-template <bool NT>
-__device__ __forceinline__ void broadcast(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
-                                          const void *src, uint64_t n, int root, int rank, int nwgs, uint64_t chunk)
-{
-    if (n == 0) return;
-    multicast_all<NT>(member0(ctx, team, dest), member_stride(ctx, team), (uint32_t)team.size,
-                      (const uint8_t *)src + (uint64_t)shmemx_team_pe(team, root) * ctx.c.stride, 0, 1, n,
-                      team_workers(ctx, team, rank, nwgs), chunk);
 }
 
 // Member p's block q <- a block of member q, n bytes each: block p of its
@@ -1102,17 +1097,29 @@ __device__ __forceinline__ void broadcast(const shmem_dctx_t &ctx, const shmemx_
 // filled batch is a round trip of its own) and take 437, blocks of 100001
 // bytes 166 and 159, 1 MiB 1480 and 1460.  Consecutive tasks go to different work-groups first, so a few
 // tiny blocks per member still spread over every work-group.
-template <bool NT, int U, bool ONE>
-__device__ __forceinline__ void pair_blocks(uint8_t *D0, const uint8_t *S0, uint64_t ps, uint32_t P, uint64_t n,
-                                            const Workers &W, uint64_t chunk)
+struct PairSplit {
+    uint64_t task, nch;   // bytes per task, tasks per block
+    uint32_t g;           // lanes per task
+};
+template <int U>
+__host__ __device__ __forceinline__ PairSplit pair_split(uint64_t n, uint32_t P, uint32_t workers, uint32_t bd, uint64_t chunk)
 {
     constexpr uint64_t kPass = 16ull * U, kBatch = 64 * kPass;   // bytes per lane and per wavefront in one pass
-    const uint64_t share = udiv(n * P * P, (uint64_t)W.n * (blockDim.x / 64) * 8);
-    const uint64_t task = min(min(chunk, n), max(kBatch, min<uint64_t>(share / kBatch * kBatch, 64u << 10)));
-    uint32_t g = 2;
-    while (g < 64 && g * kPass < task) g <<= 1;
-    const uint64_t nch = udiv(n + task - 1, task);
-    const uint64_t ntask = nch * P * P;
+    // (Work-groups below a wavefront count as one.)
+    const uint64_t share = udiv(n * P * P, (uint64_t)workers * most(bd / 64, 1) * 8);
+    PairSplit m;
+    m.task = least(least(chunk, n), most(kBatch, least(share / kBatch * kBatch, 64u << 10)));
+    m.g = 2;
+    while (m.g < 64 && m.g * kPass < m.task) m.g <<= 1;
+    m.nch = udiv(n + m.task - 1, m.task);
+    return m;
+}
+template <bool NT, int U, bool ONE>
+__device__ __forceinline__ void pair_blocks(uint8_t *D0, const uint8_t *S0, uint64_t ps, uint32_t P, uint64_t n,
+                                            const Workers &W, const PairSplit &m)
+{
+    const uint64_t task = m.task, nch = m.nch, ntask = nch * P * P;
+    const uint32_t g = m.g;
     const uint32_t mine = threadIdx.x / g, lane = threadIdx.x % g, groups = blockDim.x / g;
     if (mine >= groups) return;   // threads past the last whole group
     for (uint64_t t = (uint64_t)mine * W.n + W.w; t < ntask; t += (uint64_t)W.n * groups) {
@@ -1125,32 +1132,9 @@ __device__ __forceinline__ void pair_blocks(uint8_t *D0, const uint8_t *S0, uint
     }
 }
 
-// Every member's dest[q*n, (q+1)*n) <- member q's src[0, n).  Blocks shorter
-// than kPairMax go from each source to each destination, many at once; longer
-// ones are read once per group of members.
+// fcollect: blocks shorter than kPairMax go from each source to each
+// destination, many at once; longer ones are read once per group of members.
 constexpr uint64_t kPairMax = 16ull << 10;
-template <bool NT>
-__device__ __forceinline__ void fcollect(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
-                                         const void *src, uint64_t n, int rank, int nwgs, uint64_t chunk)
-{
-    if (n == 0) return;
-    const Workers W = team_workers(ctx, team, rank, nwgs);
-    const uint8_t *S0 = member0(ctx, team, src);
-    uint8_t *D = member0(ctx, team, dest);
-    const uint64_t ps = member_stride(ctx, team);
-    if (n < kPairMax) pair_blocks<NT, 4, true>(D, S0, ps, (uint32_t)team.size, n, W, chunk);
-    else multicast_all<NT>(D, ps, (uint32_t)team.size, S0, ps, (uint32_t)team.size, n, W, chunk);
-}
-
-// Member p's dest[q*n, (q+1)*n) <- member q's src[p*n, (p+1)*n).
-template <bool NT, int U>
-__device__ __forceinline__ void alltoall(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
-                                         const void *src, uint64_t n, int rank, int nwgs, uint64_t chunk)
-{
-    if (n == 0) return;
-    pair_blocks<NT, U, false>(member0(ctx, team, dest), member0(ctx, team, src), member_stride(ctx, team),
-                              (uint32_t)team.size, n, team_workers(ctx, team, rank, nwgs), chunk);
-}
 
 // TREE in streaming form.  Pushing x_0, x_1, ... keeps, for every set bit j
 // of the count, the reduction of an aligned block of 2^j consecutive inputs
@@ -1304,11 +1288,10 @@ struct CodecBF16 {
 struct RedRange {
     uint64_t head, nvec;
 };
-template <int ES>
-__device__ __forceinline__ RedRange red_range(const uint8_t *d0, uint64_t nelem)
+__host__ __device__ __forceinline__ RedRange red_range(const uint8_t *d0, uint64_t nelem, uint32_t ES)
 {
     const uint64_t dm = (uintptr_t)d0 & 15;
-    const uint64_t head = dm % ES ? 0 : min<uint64_t>(((16 - dm) & 15) / ES, nelem);
+    const uint64_t head = dm % ES ? 0 : least(((16 - dm) & 15) / ES, nelem);
     return RedRange{head, (nelem - head) * ES / 16};
 }
 
@@ -1373,35 +1356,39 @@ __device__ __forceinline__ void reduce_singles(int P, uint64_t pstride, const ui
 // member's page, so each address translation serves K KiB instead of 1
 // KiB: the member walk visits 2P pages per vector, more than a CU's
 // first-level translation cache holds.  LEVELS bounds the team size
-// (2^LEVELS - 1 members); larger teams get SHMEMX_ERR_UNSUPPORTED.
-template <class CODEC, class OP, bool NT, int K = 1, int LEVELS = kTreeLevels>
-__device__ __forceinline__ int reduce(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
-                                      const void *src, uint64_t nelem, int rank, int nwgs, uint64_t chunk)
+// (2^LEVELS - 1 members).
+struct RedSplit {
+    RedRange range;
+    uint64_t vpt, ntask;   // vectors per task, tasks
+};
+__host__ __device__ __forceinline__ RedSplit red_split(const uint8_t *d0, uint64_t nelem, uint32_t ES, uint32_t workers,
+                                                       uint64_t chunk)
 {
-    using A = typename CODEC::A;
-    constexpr int E = CODEC::E;
-    constexpr int B = kRedBatch / K > 0 ? kRedBatch / K : 1;   // members per load batch
-    if (team.size >= (1 << LEVELS)) return SHMEMX_ERR_UNSUPPORTED;
-    const Workers W = team_workers(ctx, team, rank, nwgs);
-    const int P = team.size;
-    const uint64_t pstride = member_stride(ctx, team);
-    const uint8_t *s0 = member0(ctx, team, src);
-    uint8_t *d0 = member0(ctx, team, dest);
-    const RedRange range = red_range<CODEC::ES>(d0, nelem);
-    const uint64_t h = range.head, nvec = range.nvec;
-    reduce_singles<CODEC, OP>(P, pstride, s0, d0, nelem, h, h + nvec * 16 / CODEC::ES, W);
-    const uint8_t *sv = s0 + h * CODEC::ES;
-    uint8_t *dv = d0 + h * CODEC::ES;
     // Vectors per task: the chunk, or an even share per worker when that is
     // smaller, so a small reduction still spreads over every work-group
     // (each element's order over the members does not depend on who runs it).
     // Shares are whole 1 KiB runs: tasks that begin off the lines' boundaries
     // write parts of lines (64 members, bf16, 4000003 elements in 512 tasks
     // of 977 vectors 208 us, of 1024 178).
-    uint64_t share = udiv(nvec + W.n - 1, W.n);
+    RedSplit m;
+    m.range = red_range(d0, nelem, ES);
+    uint64_t share = udiv(m.range.nvec + workers - 1, workers);
     if (share > 64) share = (share + 63) & ~63ull;
-    const uint64_t vpt = max<uint64_t>(1, min<uint64_t>(chunk / 16, share));
-    const uint64_t ntask = udiv(nvec + vpt - 1, vpt);
+    m.vpt = most(1, least(chunk / 16, share));
+    m.ntask = udiv(m.range.nvec + m.vpt - 1, m.vpt);
+    return m;
+}
+template <class CODEC, class OP, bool NT, int K = 1, int LEVELS = kTreeLevels>
+__device__ __forceinline__ void reduce(uint8_t *d0, const uint8_t *s0, uint64_t pstride, int P, uint64_t nelem,
+                                       const Workers &W, const RedSplit &m)
+{
+    using A = typename CODEC::A;
+    constexpr int E = CODEC::E;
+    constexpr int B = kRedBatch / K > 0 ? kRedBatch / K : 1;   // members per load batch
+    const uint64_t h = m.range.head, nvec = m.range.nvec, vpt = m.vpt, ntask = m.ntask;
+    reduce_singles<CODEC, OP>(P, pstride, s0, d0, nelem, h, h + nvec * 16 / CODEC::ES, W);
+    const uint8_t *sv = s0 + h * CODEC::ES;
+    uint8_t *dv = d0 + h * CODEC::ES;
     const uint64_t bd = blockDim.x;
     for (uint64_t t = W.w; t < ntask; t += W.n) {
         const uint64_t v1 = min(nvec, (t + 1) * vpt);
@@ -1442,7 +1429,6 @@ __device__ __forceinline__ int reduce(const shmem_dctx_t &ctx, const shmemx_dtea
                     if (i + k * bd < v1) st_any<NT, v4u>(dp + k * bd * 16, out[k]);
         }
     }
-    return 0;
 }
 
 // Reduce-to-all with the team's members split over the work-group's
@@ -1461,35 +1447,47 @@ __device__ __forceinline__ int reduce(const shmem_dctx_t &ctx, const shmemx_dtea
 // are double-buffered, so one barrier per step suffices.  Every thread of
 // the work-group calls it; blockDim.x is a multiple of 64, at most
 // 64 * kRedWaveMax.
+// Bound by latency where it is chosen by itself (a tile or two per
+// work-group): a block's loads are under no condition and the fold of the
+// block results is unrolled, 64 members, 4096 elements of fp32 6.6 -> 5.1 us.
+// (Block and tile in scalar registers take 81 registers instead of 142, but
+// 0.7 us more.)
 constexpr int kRedWaveMax = 8;
 
+struct RedWavesSplit {
+    RedRange range;
+    uint64_t tpt, ntask;   // tiles of 64 vectors per task, tasks
+    uint32_t m, G;         // member blocks, tiles per step
+};
+__host__ __forceinline__ RedWavesSplit red_waves_split(const uint8_t *d0, uint64_t nelem, uint32_t ES, uint32_t P,
+                                                       uint32_t waves, uint64_t chunk)
+{
+    RedWavesSplit k;
+    k.range = red_range(d0, nelem, ES);
+    k.tpt = chunk >= 1024 ? chunk / 1024 : 1;
+    k.ntask = ((k.range.nvec + 63) / 64 + k.tpt - 1) / k.tpt;
+    k.m = (P + 7) / 8;
+    k.G = waves / k.m;
+    return k;
+}
 template <class CODEC, class OP, bool NT>
-__device__ __forceinline__ void reduce_waves(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, void *dest,
-                                             const void *src, uint64_t nelem, int rank, int nwgs, uint64_t chunk)
+__device__ __forceinline__ void reduce_waves(uint8_t *d0, const uint8_t *s0, uint64_t pstride, int P, uint64_t nelem,
+                                             const Workers &W, const RedWavesSplit &k)
 {
     using A = typename CODEC::A;
     constexpr int E = CODEC::E;
     __shared__ A part[2][kRedWaveMax][E][64];
-    const Workers W = team_workers(ctx, team, rank, nwgs);
-    const int P = team.size;
-    const uint32_t waves = blockDim.x / 64, w = threadIdx.x / 64, lane = __lane_id();
-    const uint32_t m = (uint32_t)(P + 7) / 8;          // member blocks
-    const uint32_t G = waves / m;                      // tiles per step
+    const uint32_t w = threadIdx.x / 64, lane = __lane_id();
+    const uint32_t m = k.m, G = k.G;
     const uint32_t j = w / m, b = w - j * m;           // this wavefront's tile slot and block
     const int p0 = 8 * (int)b, p1 = min(p0 + 8, P);
-    const uint64_t pstride = member_stride(ctx, team);
-    const uint8_t *s0 = member0(ctx, team, src);
-    uint8_t *d0 = member0(ctx, team, dest);
-    const RedRange range = red_range<CODEC::ES>(d0, nelem);
-    const uint64_t h = range.head, nvec = range.nvec;
+    const uint64_t h = k.range.head, nvec = k.range.nvec;
     reduce_singles<CODEC, OP>(P, pstride, s0, d0, nelem, h, h + nvec * 16 / CODEC::ES, W);
     const uint8_t *sv = s0 + h * CODEC::ES;
     uint8_t *dv = d0 + h * CODEC::ES;
     // Tasks of `chunk` bytes per member (whole tiles of 64 vectors), dealt to
     // the workers round robin; a worker walks its task's tiles in order.
-    const uint64_t ntile = (nvec + 63) / 64;
-    const uint64_t tpt = chunk >= 1024 ? chunk / 1024 : 1;
-    const uint64_t ntask = (ntile + tpt - 1) / tpt;
+    const uint64_t ntile = (nvec + 63) / 64, tpt = k.tpt, ntask = k.ntask;
     int buf = 0;
     for (uint64_t task = W.w; task < ntask; task += W.n)
     for (uint64_t t0 = task * tpt; t0 < (task + 1) * tpt && t0 < ntile; t0 += G) {
@@ -1497,10 +1495,10 @@ __device__ __forceinline__ void reduce_waves(const shmem_dctx_t &ctx, const shme
         const bool mine = j < G && t0 + j < (task + 1) * tpt && i < nvec;
         if (mine) {
             const uint8_t *sp = sv + i * 16 + (uint64_t)p0 * pstride;
-            v4u raw[8];
+            v4u raw[8];   // (a short block's last member again: no load under a condition of its own)
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (p0 + u < p1) raw[u] = ld_any<NT, v4u>(sp + (uint64_t)u * pstride);
+            for (int u = 0; u < 8; ++u) raw[u] = ld_any<NT, v4u>(sp + (uint64_t)min(u, p1 - p0 - 1) * pstride);
+            loads_issued();
             TreeAcc<A, E, OP, 4> acc;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -1518,11 +1516,14 @@ __device__ __forceinline__ void reduce_waves(const shmem_dctx_t &ctx, const shme
         __syncthreads();
         if (mine) {
             TreeAcc<A, E, OP, 4> acc;
-            for (uint32_t bb = 0; bb < m; ++bb) {
-                A x[E];
 #pragma unroll
-                for (int e = 0; e < E; ++e) x[e] = part[buf][j * m + bb][e][lane];
-                acc.push(bb, x);
+            for (uint32_t bb = 0; bb < kRedWaveMax; ++bb) {
+                if (bb < m) {
+                    A x[E];
+#pragma unroll
+                    for (int e = 0; e < E; ++e) x[e] = part[buf][j * m + bb][e][lane];
+                    acc.push(bb, x);
+                }
             }
             A r[E];
             acc.result(m, r);
@@ -1585,7 +1586,14 @@ __device__ __forceinline__ int shmemx_broadcastmem_grid(const shmem_dctx_t &ctx,
                                 n, ((uint64_t)(uint32_t)nwgs << 32) | (uint32_t)root))
         return SHMEMX_ERR_ARG;
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
-    vshmem_detail::broadcast<false>(ctx, team, dest, src, n, root, rank, nwgs, vshmem_detail::kCollChunk);
+    if (n) {
+        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
+        const uint64_t ps = vshmem_detail::member_stride(ctx, team);
+        const uint32_t P = (uint32_t)team.size;
+        vshmem_detail::multicast_all<false>(vshmem_detail::member0(ctx, team, dest), ps, P,
+                                            vshmem_detail::member0(ctx, team, src) + (uint64_t)root * ps, 0, 1, n, W,
+                                            vshmem_detail::mcast_split(n, 1, P, W.n, vshmem_detail::kCollChunk));
+    }
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
@@ -1601,7 +1609,19 @@ __device__ __forceinline__ int shmemx_fcollectmem_grid(const shmem_dctx_t &ctx, 
                                 (uint64_t)nwgs))
         return SHMEMX_ERR_ARG;
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
-    vshmem_detail::fcollect<false>(ctx, team, dest, src, n, rank, nwgs, vshmem_detail::kCollChunk);
+    if (n) {
+        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
+        const uint64_t ps = vshmem_detail::member_stride(ctx, team);
+        const uint32_t P = (uint32_t)team.size;
+        uint8_t *D = vshmem_detail::member0(ctx, team, dest);
+        const uint8_t *S = vshmem_detail::member0(ctx, team, src);
+        if (n < vshmem_detail::kPairMax)
+            vshmem_detail::pair_blocks<false, 4, true>(
+                D, S, ps, P, n, W, vshmem_detail::pair_split<4>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk));
+        else
+            vshmem_detail::multicast_all<false>(D, ps, P, S, ps, P, n, W,
+                                                vshmem_detail::mcast_split(n, P, P, W.n, vshmem_detail::kCollChunk));
+    }
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
@@ -1617,7 +1637,14 @@ __device__ __forceinline__ int shmemx_alltoallmem_grid(const shmem_dctx_t &ctx, 
                                 rank >= 0 && rank < nwgs, n, (uint64_t)nwgs))
         return SHMEMX_ERR_ARG;
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
-    vshmem_detail::alltoall<true, 8>(ctx, team, dest, src, n, rank, nwgs, vshmem_detail::kCollChunk);
+    if (n) {
+        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
+        const uint32_t P = (uint32_t)team.size;
+        vshmem_detail::pair_blocks<true, 8, false>(
+            vshmem_detail::member0(ctx, team, dest), vshmem_detail::member0(ctx, team, src),
+            vshmem_detail::member_stride(ctx, team), P, n, W,
+            vshmem_detail::pair_split<8>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk));
+    }
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
@@ -1637,8 +1664,11 @@ __device__ __forceinline__ int shmem_alltoallmem_wg(const shmem_dctx_t &ctx, con
             return SHMEMX_ERR_ARG;                                                                                 \
         if (team.size >= (1 << vshmem_detail::kTreeLevels)) return SHMEMX_ERR_UNSUPPORTED;                         \
         shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);                                                         \
-        (void)vshmem_detail::reduce<vshmem_detail::CODEC, vshmem_detail::OP, true>(                                \
-            ctx, team, dest, src, nreduce, rank, nwgs, vshmem_detail::kRedChunk);                                  \
+        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);                      \
+        uint8_t *D = vshmem_detail::member0(ctx, team, dest);                                                      \
+        vshmem_detail::reduce<vshmem_detail::CODEC, vshmem_detail::OP, true>(                                      \
+            D, vshmem_detail::member0(ctx, team, src), vshmem_detail::member_stride(ctx, team), team.size, nreduce, \
+            W, vshmem_detail::red_split(D, nreduce, sizeof(T), W.n, vshmem_detail::kRedChunk));                    \
         shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);                                                         \
         return 0;                                                                                                  \
     }

@@ -18,85 +18,63 @@ using vshmem_detail::CodecI64;
 using vshmem_detail::OpMax;
 using vshmem_detail::OpSum;
 
-struct Geo {
-    shmemx_dctx_pub_t c;
-    shmemx_dteam_t team;
-    uint64_t dst_off, src_off;
+// What a collective's kernel gets: member 0's destination and source, the
+// distance between members' copies, the work, and how it is cut.
+struct Coll {
+    uint8_t *D;
+    const uint8_t *S;
+    uint64_t ps;
     uint64_t n;          // bytes per block (elements for reduce)
-    uint64_t chunk;      // bytes per task
-    int wgs_per_pe;
+    uint32_t P;
 };
 
 // The library's launches run the device collectives' bodies, without their
 // opening and closing team barriers: nothing inside a collective depends on
 // another work-group's stores, the launch follows all earlier work of its
 // stream, and its end completes every store.  With them a reduction of 16 fp32
-// elements over 64 PEs took 15.6 us, and takes 10.6 without.  Work-group b acts for team
-// member b / wgs_per_pe, as its rank b % wgs_per_pe.
-struct Caller {
-    shmem_dctx_t ctx;
-    void *dst;
-    const void *src;
-    int rank;
-};
+// elements over 64 PEs took 15.6 us, and took 10.6 without.  Work-group b is
+// worker b.
+__device__ __forceinline__ vshmem_detail::Workers workers() { return vshmem_detail::Workers{blockIdx.x, gridDim.x}; }
 
-__device__ __forceinline__ Caller caller(const Geo &g)
-{
-    const int k = (int)(blockIdx.x / (unsigned)g.wgs_per_pe);
-    return Caller{shmemx_dctx_bind(g.c, shmemx_team_pe(g.team, k)), g.c.base + g.dst_off, g.c.base + g.src_off,
-                  (int)(blockIdx.x - (unsigned)k * (unsigned)g.wgs_per_pe)};
-}
-
+// Broadcast (Q = 1, S the root's source) and fcollect of long blocks (Q = P).
 template <bool NT>
-__global__ void __launch_bounds__(1024) k_broadcast(Geo g, int root)
+__global__ void __launch_bounds__(1024) k_multicast(Coll g, uint64_t sstep, uint32_t Q, vshmem_detail::McastSplit m)
 {
-    const Caller a = caller(g);
-    vshmem_detail::broadcast<NT>(a.ctx, g.team, a.dst, a.src, g.n, root, a.rank, g.wgs_per_pe, g.chunk);
+    vshmem_detail::multicast_all<NT>(g.D, g.ps, g.P, g.S, sstep, Q, g.n, workers(), m);
 }
 
-template <bool NT>
-__global__ void __launch_bounds__(1024) k_fcollect(Geo g)
+// Alltoall, and fcollect of short blocks (ONE).
+template <bool NT, int U, bool ONE>
+__global__ void __launch_bounds__(1024) k_pairs(Coll g, vshmem_detail::PairSplit m)
 {
-    const Caller a = caller(g);
-    vshmem_detail::fcollect<NT>(a.ctx, g.team, a.dst, a.src, g.n, a.rank, g.wgs_per_pe, g.chunk);
-}
-
-template <bool NT, int U>
-__global__ void __launch_bounds__(1024) k_alltoall(Geo g)
-{
-    const Caller a = caller(g);
-    vshmem_detail::alltoall<NT, U>(a.ctx, g.team, a.dst, a.src, g.n, a.rank, g.wgs_per_pe, g.chunk);
+    vshmem_detail::pair_blocks<NT, U, ONE>(g.D, g.S, g.ps, g.P, g.n, workers(), m);
 }
 
 template <class CODEC, class OP, bool NT>
-__global__ void __launch_bounds__(256) k_reduce(Geo g)
+__global__ void __launch_bounds__(256) k_reduce(Coll g, vshmem_detail::RedSplit m)
 {
-    const Caller a = caller(g);
-    (void)vshmem_detail::reduce<CODEC, OP, NT>(a.ctx, g.team, a.dst, a.src, g.n, a.rank, g.wgs_per_pe, g.chunk);
+    vshmem_detail::reduce<CODEC, OP, NT>(g.D, g.S, g.ps, (int)g.P, g.n, workers(), m);
 }
 
 // Two vectors per lane and a TREE stack for teams of up to 127 members.
 template <class CODEC, class OP, bool NT>
-__global__ void __launch_bounds__(256) k_reduce2(Geo g)
+__global__ void __launch_bounds__(256) k_reduce2(Coll g, vshmem_detail::RedSplit m)
 {
-    const Caller a = caller(g);
-    (void)vshmem_detail::reduce<CODEC, OP, NT, 2, 7>(a.ctx, g.team, a.dst, a.src, g.n, a.rank, g.wgs_per_pe,
-                                                      g.chunk);
+    vshmem_detail::reduce<CODEC, OP, NT, 2, 7>(g.D, g.S, g.ps, (int)g.P, g.n, workers(), m);
 }
 
 template <class CODEC, class OP, bool NT>
-__global__ void __launch_bounds__(64 * vshmem_detail::kRedWaveMax) k_reduce_waves(Geo g)
+__global__ void __launch_bounds__(64 * vshmem_detail::kRedWaveMax) k_reduce_waves(Coll g, vshmem_detail::RedWavesSplit m)
 {
-    const Caller a = caller(g);
-    vshmem_detail::reduce_waves<CODEC, OP, NT>(a.ctx, g.team, a.dst, a.src, g.n, a.rank, g.wgs_per_pe, g.chunk);
+    vshmem_detail::reduce_waves<CODEC, OP, NT>(g.D, g.S, g.ps, (int)g.P, g.n, workers(), m);
 }
 
 // ------------------------------------------------------------- launching
 // Bytes a member writes per automatically added work-group: one pass of 1024
 // lanes.  A further work-group costs its dispatch only, now that it is no
-// barrier arrival: 64 PEs, alltoall of 4 KiB blocks takes 7.4 us with four
-// per member (the rate at which the host launches), broadcast of 64 KiB 7.1
-// with four; both had one, between barriers, and took 15.4 and 46.5.
+// barrier arrival: 64 PEs, alltoall of 4 KiB blocks takes 5.7 us with four
+// per member, broadcast of 64 KiB 4.1 (the rate of the launches) with four;
+// both had one, between barriers, and took 15.4 and 46.5.
 constexpr uint64_t kAutoBytesPerWg = 16ull << 10;
 
 // Wavefronts per CU that a launch of each collective may count on.  The
@@ -106,6 +84,22 @@ constexpr uint64_t kAutoBytesPerWg = 16ull << 10;
 constexpr int kWavesBroadcast = 16, kWavesFcollect = 20, kWavesAlltoallDeep = 20, kWavesAlltoall = 32;
 constexpr int kWavesReduce = 20, kWavesReduceBf16 = 12, kWavesReduce2 = 16, kWavesReduce2Bf16 = 8;
 constexpr int kWavesReduceSplit = 16, kWavesReduceSplitBf16 = 12;
+
+struct Geo {
+    shmemx_dctx_pub_t c;
+    shmemx_dteam_t team;
+    uint64_t dst_off, src_off;
+    uint64_t n;          // bytes per block (elements for reduce)
+    uint64_t chunk;      // bytes per task
+    int wgs_per_pe;
+
+    Coll coll() const
+    {
+        const uint64_t first = (uint64_t)team.start * c.stride;
+        return Coll{c.base + first + dst_off, c.base + first + src_off, (uint64_t)team.stride * c.stride, n,
+                    (uint32_t)team.size};
+    }
+};
 
 // CUs the progress kernel leaves free.
 int64_t free_cus() { return std::max(0, st().num_cus - progress_reserved_cus()); }
@@ -121,18 +115,23 @@ int64_t movement_wgs(const Geo &g, uint64_t bytes_per_member)
     return std::min<int64_t>(free_cus(), (int64_t)std::min<uint64_t>(by_bytes, 1u << 20) * g.team.size);
 }
 
-// Launch a collective's kernel.  When the caller left wgs_per_pe at 0, with
-// about auto_wgs work-groups, a whole number per member, and never more than
-// `waves` wavefronts per CU hold.
-template <typename K, typename... Args>
-int launch_team_kernel(K kernel, int waves, Geo &g, int wg, hipStream_t s, int64_t auto_wgs, Args... args)
+// Work-groups of a collective's launch, 0 (with the last error set) when it is
+// refused.  When the caller left wgs_per_pe at 0, about auto_wgs, a whole
+// number per member, and never more than `waves` wavefronts per CU hold.
+unsigned team_grid(int waves, Geo &g, int wg, int64_t auto_wgs, int *rc)
 {
     const int per_cu = std::max(1, waves * 64 / wg);
     if (g.wgs_per_pe == 0)
         g.wgs_per_pe = (int)std::max<int64_t>(1, std::min<int64_t>(auto_wgs, per_cu * free_cus()) / g.team.size);
     const int grid = g.wgs_per_pe * g.team.size;
-    if (int rc = check_resident(per_cu, grid, wg, "team collective")) return rc;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(wg), 0, s, g, args...);
+    *rc = check_resident(per_cu, grid, wg, "team collective");
+    return *rc ? 0 : (unsigned)grid;
+}
+
+template <typename K, typename... Args>
+int run(K kernel, unsigned grid, int wg, void *stream, Args... args)
+{
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(wg), 0, (hipStream_t)stream, args...);
     VSHMEM_HIP(hipGetLastError());
     return SHMEMX_OK;
 }
@@ -175,9 +174,13 @@ int shmemx_broadcastmem_launch(shmem_team_t team, void *dest, const void *src, s
         return rc;
     }
     g.n = n;
-    if (L.flags & SHMEMX_LAUNCH_NONTEMPORAL)
-        return launch_team_kernel(k_broadcast<true>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, n), root);
-    return launch_team_kernel(k_broadcast<false>, kWavesBroadcast, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, n), root);
+    const unsigned grid = team_grid(kWavesBroadcast, g, L.wg_size, movement_wgs(g, n), &rc);
+    if (rc || n == 0) return rc;
+    Coll k = g.coll();
+    k.S += (uint64_t)root * k.ps;
+    const vshmem_detail::McastSplit m = vshmem_detail::mcast_split(n, 1, k.P, grid, g.chunk);
+    const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
+    return run(nt ? k_multicast<true> : k_multicast<false>, grid, L.wg_size, stream, k, (uint64_t)0, 1u, m);
 }
 
 int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, size_t n, const shmemx_launch_t *launch,
@@ -196,9 +199,16 @@ int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, si
         return rc;
     }
     g.n = n;
-    if (L.flags & SHMEMX_LAUNCH_NONTEMPORAL)
-        return launch_team_kernel(k_fcollect<true>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, (uint64_t)n * tsize));
-    return launch_team_kernel(k_fcollect<false>, kWavesFcollect, g, L.wg_size, (hipStream_t)stream, movement_wgs(g, (uint64_t)n * tsize));
+    const unsigned grid = team_grid(kWavesFcollect, g, L.wg_size, movement_wgs(g, (uint64_t)n * tsize), &rc);
+    if (rc || n == 0) return rc;
+    const Coll k = g.coll();
+    const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
+    if (n < vshmem_detail::kPairMax) {
+        const vshmem_detail::PairSplit m = vshmem_detail::pair_split<4>(n, k.P, grid, (uint32_t)L.wg_size, g.chunk);
+        return run(nt ? k_pairs<true, 4, true> : k_pairs<false, 4, true>, grid, L.wg_size, stream, k, m);
+    }
+    const vshmem_detail::McastSplit m = vshmem_detail::mcast_split(n, k.P, k.P, grid, g.chunk);
+    return run(nt ? k_multicast<true> : k_multicast<false>, grid, L.wg_size, stream, k, k.ps, k.P, m);
 }
 
 int shmemx_alltoallmem_launch(shmem_team_t team, void *dest, const void *src, size_t n, const shmemx_launch_t *launch,
@@ -219,12 +229,15 @@ int shmemx_alltoallmem_launch(shmem_team_t team, void *dest, const void *src, si
     }
     g.n = n;
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0, deep = (L.flags & SHMEMX_LAUNCH_DEEP) != 0;
-    hipStream_t hs = (hipStream_t)stream;
-    const int64_t aw = movement_wgs(g, (uint64_t)n * tsize);
-    if (nt && deep) return launch_team_kernel(k_alltoall<true, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw);
-    if (nt) return launch_team_kernel(k_alltoall<true, 4>, kWavesAlltoall, g, L.wg_size, hs, aw);
-    if (deep) return launch_team_kernel(k_alltoall<false, 8>, kWavesAlltoallDeep, g, L.wg_size, hs, aw);
-    return launch_team_kernel(k_alltoall<false, 4>, kWavesAlltoall, g, L.wg_size, hs, aw);
+    const unsigned grid =
+        team_grid(deep ? kWavesAlltoallDeep : kWavesAlltoall, g, L.wg_size, movement_wgs(g, (uint64_t)n * tsize), &rc);
+    if (rc || n == 0) return rc;
+    const Coll k = g.coll();
+    const uint32_t bd = (uint32_t)L.wg_size;
+    const vshmem_detail::PairSplit m = deep ? vshmem_detail::pair_split<8>(n, k.P, grid, bd, g.chunk)
+                                            : vshmem_detail::pair_split<4>(n, k.P, grid, bd, g.chunk);
+    if (nt) return run(deep ? k_pairs<true, 8, false> : k_pairs<true, 4, false>, grid, L.wg_size, stream, k, m);
+    return run(deep ? k_pairs<false, 8, false> : k_pairs<false, 4, false>, grid, L.wg_size, stream, k, m);
 }
 
 int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const void *src, size_t nreduce,
@@ -257,20 +270,23 @@ int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const
         return rc;
     }
     g.n = nreduce;
-    hipStream_t s = (hipStream_t)stream;
     const bool bf = dtype == SHMEMX_DT_BF16;
     const int64_t P = g.team.size, nvec = (int64_t)(nreduce * es / 16);
     // Without a shape from the caller: a reduction with fewer vectors than
-    // half the lanes of a 256-thread work-group per CU leaves lanes idle and
-    // is a chain of P / 8 load batches in each of the others.  Splitting the
-    // members over wavefronts makes it one batch: 64 members, fp32, 16384
-    // vectors 13.2 -> 9.6 us, bf16, 8192 vectors 16.3 -> 8.5, 16 elements
-    // 10.7 -> 7.6 (the launch); at 65536 vectors the split form is the slower
-    // one (37 us against 25), and so it is for 13 members, two batches (9.8
-    // against 7.7 at 16384 vectors).
+    // lanes of a 256-thread work-group per CU leaves lanes idle and is a chain
+    // of P / 8 load batches in each of the others.  Splitting the members over
+    // wavefronts makes it one batch.  64 members: 8192 vectors of fp32 11.3 ->
+    // 5.6 us, of bf16 15.6 -> 6.4; 40960 of fp32 20.0 -> 16.5; 65536 23.0 ->
+    // 24.6; 57 members 49152 19.2 -> 20.2, so up to five eighths of the lanes.
+    // 40 members (three of eight wavefronts idle): 32768 11.3 -> 8.7, 49152
+    // 12.7 -> 14.8, so half.  24 and 29 members, two tiles per step: 8192 6.3 ->
+    // 5.8, 24576 6.0 -> 5.75, 32768 6.0 -> 6.6, so three eighths.  17 members:
+    // 8192 4.7 and 4.7, bf16 at 16384 5.5 -> 5.8; 13 members 3.8 -> 5.7: not
+    // split.
+    const int eighths = P > 56 ? 5 : P >= 32 ? 4 : P >= 24 ? 3 : 0;
     const int split_cu = (bf ? kWavesReduceSplitBf16 : kWavesReduceSplit) * 64 / 512;
     if (!waves && !two && (!launch || (launch->wgs_per_pe == 0 && launch->wg_size == 0 && launch->chunk_bytes == 0)) &&
-        P >= 32 && P <= 64 && 2 * nvec <= free_cus() * 256 && split_cu * free_cus() >= P) {
+        eighths && P <= 64 && 8 * nvec <= eighths * free_cus() * 256 && split_cu * free_cus() >= P) {
         waves = true;
         L.wg_size = 512;
         g.chunk = 1024;   // one tile of 64 vectors
@@ -282,19 +298,26 @@ int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const
     const int64_t per_step = waves ? 64 * std::max<int64_t>(1, 8 / ((P + 7) / 8)) : 128;
     const int64_t aw = std::min<int64_t>((nvec <= 2048 * free_cus() ? 2 : 1) * free_cus(), (nvec + per_step * P - 1) / (per_step * P) * P);
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
-#define VSHMEM_RED_K(K, W, CODEC)                                                                           \
-    do {                                                                                                    \
-        const int w_ = bf ? W##Bf16 : W;                                                                    \
-        if (op == SHMEMX_RED_SUM)                                                                           \
-            return nt ? launch_team_kernel(K<CODEC, OpSum, true>, w_, g, L.wg_size, s, aw)              \
-                      : launch_team_kernel(K<CODEC, OpSum, false>, w_, g, L.wg_size, s, aw);            \
-        return nt ? launch_team_kernel(K<CODEC, OpMax, true>, w_, g, L.wg_size, s, aw)                  \
-                  : launch_team_kernel(K<CODEC, OpMax, false>, w_, g, L.wg_size, s, aw);                \
+    const int per_cu = waves ? (bf ? kWavesReduceSplitBf16 : kWavesReduceSplit)
+                       : two ? (bf ? kWavesReduce2Bf16 : kWavesReduce2)
+                             : (bf ? kWavesReduceBf16 : kWavesReduce);
+    const unsigned grid = team_grid(per_cu, g, L.wg_size, aw, &rc);
+    if (rc) return rc;
+    const Coll k = g.coll();
+    const vshmem_detail::RedSplit m = vshmem_detail::red_split(k.D, nreduce, (uint32_t)es, grid, g.chunk);
+    const vshmem_detail::RedWavesSplit mw =
+        waves ? vshmem_detail::red_waves_split(k.D, nreduce, (uint32_t)es, k.P, (uint32_t)L.wg_size / 64, g.chunk)
+              : vshmem_detail::RedWavesSplit{};
+#define VSHMEM_RED_K(K, SPLIT, CODEC)                                                                     \
+    do {                                                                                                  \
+        if (op == SHMEMX_RED_SUM)                                                                         \
+            return run(nt ? K<CODEC, OpSum, true> : K<CODEC, OpSum, false>, grid, L.wg_size, stream, k, SPLIT); \
+        return run(nt ? K<CODEC, OpMax, true> : K<CODEC, OpMax, false>, grid, L.wg_size, stream, k, SPLIT); \
     } while (0)
-#define VSHMEM_RED(CODEC)                                                                                   \
-    if (waves) VSHMEM_RED_K(k_reduce_waves, kWavesReduceSplit, CODEC);                                      \
-    if (two) VSHMEM_RED_K(k_reduce2, kWavesReduce2, CODEC);                                                 \
-    VSHMEM_RED_K(k_reduce, kWavesReduce, CODEC);
+#define VSHMEM_RED(CODEC)                                                                                 \
+    if (waves) VSHMEM_RED_K(k_reduce_waves, mw, CODEC);                                                   \
+    if (two) VSHMEM_RED_K(k_reduce2, m, CODEC);                                                           \
+    VSHMEM_RED_K(k_reduce, m, CODEC);
     if (dtype == SHMEMX_DT_INT64) {
         VSHMEM_RED(CodecI64)
     } else if (dtype == SHMEMX_DT_FP32) {

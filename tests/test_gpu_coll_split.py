@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 import workload as W
-from tests.gpu_helpers import assert_no_device_errors, download, heap, upload
+from tests.gpu_helpers import assert_no_device_errors, download, heap, torch, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -79,4 +79,30 @@ def test_reductions_at_every_offset(dt, npes):
                     ref = init.copy()
                     oracle.reduce(ref, dt, rop, do + b, so + a, n)
                     assert np.array_equal(download(region), ref), (n, a, b, launch is None)
+        assert_no_device_errors()
+
+
+@pytest.mark.parametrize("npes,eighths", [(23, 3), (24, 3), (33, 4), (56, 4), (57, 5), (64, 5)])
+def test_reductions_split_over_wavefronts(npes, eighths):
+    """Teams on both sides of those whose small reductions split the members
+    over wavefronts, with the vectors of a launch around its limit: bit-exact
+    against the oracle, in place as well."""
+    with heap(npes, 2 << 20) as v:
+        cus = torch().cuda.get_device_properties(0).multi_processor_count
+        limit = eighths * cus * 32
+        room = (limit + 1) * 16
+        src, dst = v.malloc(room), v.malloc(room)
+        so, do = v.offset(src), v.offset(dst)
+        for dt, es, gen in ((oracle.DT_FP32, 4, W.coll_f32), (oracle.DT_BF16, 2, W.coll_bf16)):
+            for nvec in (63, 65, limit, limit + 1):
+                n = nvec * 16 // es
+                init = W.heap_fill(0xD8, npes, do + room)
+                for p in range(npes):
+                    init[p, so:so + n * es] = np.ascontiguousarray(gen(0xD7, p, n)).view(np.uint8)
+                for to, off in ((dst, do), (src, so)):
+                    upload(init)
+                    v.reduce(dt, oracle.RO_SUM, to, src, n)
+                    ref = init.copy()
+                    oracle.reduce(ref, dt, oracle.RO_SUM, off, so, n)
+                    assert np.array_equal(download(do + room), ref), (dt, nvec, to == src)
         assert_no_device_errors()
