@@ -178,13 +178,13 @@ def build_rows(v, torch, L: Layout, npes: int, want):
     # ---- collectives (a7-a10)
     blk = int(1 * MiB * min(1.0, scale))
     add("alltoall_1MiB_fp32", lambda: v.alltoallmem(L.addr(L.B), L.addr(L.C), blk), 2 * npes * npes * blk,
-        kernel="k_alltoall<true,8>")
+        kernel="k_pairs<true,8,false>")
     fc = int(4 * MiB * min(1.0, scale))
     add("fcollect_4MiB", lambda: v.fcollectmem(L.addr(L.B), L.addr(L.C), fc), npes * fc + npes * npes * fc,
-        kernel="k_fcollect<false>")
+        kernel="k_multicast<false>")
     bc = L.D - L.C
     add("broadcast_256MiB", lambda: v.broadcastmem(L.addr(L.B), L.addr(L.C), bc, 0), bc + npes * bc,
-        kernel="k_broadcast<false>")
+        kernel="k_multicast<false>")
     nred = (L.E - L.D) // 8
     for dt, src, es, tag, codec in ((v.DT_INT64, L.D, 8, "i64", "CodecI64"), (v.DT_FP32, L.E, 4, "f32", "CodecF32"),
                                     (v.DT_BF16, L.F, 2, "bf16", "CodecBF16")):
@@ -288,9 +288,8 @@ def percentile(a, q):
 # the committed counter figures stale.
 KERNEL_SOURCES = {
     "k_rma_pattern": ["paper_2607_08006_amd/csrc/rma.hip"],
-    "k_alltoall": ["paper_2607_08006_amd/csrc/coll.hip"],
-    "k_broadcast": ["paper_2607_08006_amd/csrc/coll.hip"],
-    "k_fcollect": ["paper_2607_08006_amd/csrc/coll.hip"],
+    "k_pairs": ["paper_2607_08006_amd/csrc/coll.hip"],
+    "k_multicast": ["paper_2607_08006_amd/csrc/coll.hip"],
     "k_reduce": ["paper_2607_08006_amd/csrc/coll.hip"],
     "k_reduce_waves": ["paper_2607_08006_amd/csrc/coll.hip"],
 }
