@@ -34,7 +34,9 @@ namespace {
 constexpr uint32_t kNone = 0xFFFFFFFFu;
 constexpr int kIndexThreads = 1024;
 constexpr int kIndexWaves = kIndexThreads / 64;
-constexpr int kClassifyThreads = 1024;      // one tile of the parallel index
+// A quarter of a tile of the parallel index: with whole tiles the descriptors'
+// loads came from fewer CUs (a launch of 4000 small puts 21.7 us, 20.4 so).
+constexpr int kClassifyThreads = 256;
 constexpr int kIndexMaxPes = 4096;          // per-issuer ordering state held in LDS
 constexpr int kIndexItems = 8;              // descriptors per index thread per tile
 constexpr uint32_t kLdsEpochs = 4096;       // epochs whose counters the index kernel keeps in LDS
@@ -47,7 +49,7 @@ constexpr uint32_t kIndexTile = kIndexThreads * kIndexItems;
 // ordering points and no operation of kParTasks or more work-group tasks (so
 // that 32 bits hold any sum of tasks).  Otherwise one work-group builds it.
 constexpr uint32_t kParTile = kIndexThreads;
-constexpr uint32_t kParTable = 65536, kParTiles = kParTable / kParTile;
+constexpr uint32_t kParTable = 65536, kParTiles = kParTable / kParTile, kParLists = kParTable / kClassifyThreads;
 constexpr uint32_t kParSync = 1024;
 constexpr uint32_t kParTasks = 65536;
 constexpr uint32_t kParBuckets = 8192;      // counters (packed count and tasks) in LDS and in memory
@@ -409,7 +411,7 @@ __device__ __forceinline__ void store_run(uint32_t *p, uint32_t i0, uint32_t n, 
 // validates the descriptor, resolves its scope and chunking, and writes its
 // class word (to the key section) and its work-group task count.  Invalid
 // descriptors latch SHMEMX_DEVERR_BAD_DESC and are skipped.  Each work-group
-// (one tile) also lists its ordering points in table order (to the eb
+// also lists its ordering points in table order (to the eb
 // section, count and a flag for operations of too many tasks to the maxf
 // section), and the counters of the parallel index are cleared.
 __global__ void __launch_bounds__(kClassifyThreads) k_batch_classify(BatchArgs a)
@@ -464,7 +466,7 @@ __global__ void __launch_bounds__(kClassifyThreads) k_batch_classify(BatchArgs a
         before += k < wave ? wcount[k] : 0;
         all += wcount[k];
     }
-    // sync_entry's position is the one inside the tile.
+    // sync_entry's position is the one inside the work-group's list.
     if (sync)
         a.w.eb[blockIdx.x * kClassifyThreads + before + (uint32_t)__builtin_popcountll(m & ((1ull << lane) - 1ull))] =
             sync_entry(threadIdx.x, type == kTypeBarrier, iss);
@@ -841,7 +843,7 @@ __device__ __forceinline__ void index_serial(const BatchArgs &a, SerialLds &L)
 // The serial form is bound by one work-group's latency, 3 ns per descriptor,
 // this one by its chain of dependent steps.  4-PE mixed program (11044
 // descriptors): 36.0 us serial; 12.2 us here and 4.7 us in the scatter kernel,
-// and the whole launch 79.0 -> 58.9 us.  Launches of 300, 16000 and 60000 small
+// and the whole launch 79.0 -> 58.2 us.  Launches of 300, 16000 and 60000 small
 // puts with 64 barriers between 4 PEs: 82.9 -> 62.6, 155 -> 99, 241 -> 106 us.
 // The dearest points are fences of PEs that seldom issue one (each operation
 // searches far back): 4000 puts, 1000 fences, 64 PEs take 183 us, 179 before.
@@ -851,20 +853,26 @@ struct ParLds {
     uint32_t epoch[kParSync + 1];       // per point: epoch after it; fences after it in the high half
     uint32_t base[kParSync + 2];        // per epoch: most fences, then first phase
     uint32_t nbar[kIndexMaxPes];
-    uint32_t first[kParTiles + 1];      // per tile: its first point
+    uint32_t first[kParLists + 1];      // per list: its first point
     uint32_t s_bad, s_big, s_last, s_max, s_lastph;
 };
 
 // cw, nch: this thread's class word and task count, read ahead.
 __device__ __forceinline__ void index_parallel(const BatchArgs &a, ParLds &L, uint32_t cw, uint32_t nch)
 {
-    const uint32_t tid = threadIdx.x, n = a.n, npts = L.first[a.tiles];
+    const uint32_t tid = threadIdx.x, n = a.n, npts = L.first[4 * a.tiles];
     const Ws &w = a.w;
     for (int p = tid; p < a.c.npes; p += kIndexThreads) L.nbar[p] = 0;
     for (uint32_t e = tid; e < kParSync + 2; e += kIndexThreads) L.base[e] = 0;
-    for (uint32_t t = tid / 64; t < a.tiles; t += kIndexWaves)
-        for (uint32_t k = __lane_id(); k < L.first[t + 1] - L.first[t]; k += 64)
-            L.point[L.first[t] + k] = w.eb[t * kParTile + k] + ((t * kParTile) << 13);
+    if (tid < npts) {
+        // A point per thread: its list is the last one that begins at or before it.
+        uint32_t t = 0;
+#pragma unroll
+        for (uint32_t step = kParLists / 2; step; step >>= 1)
+            if (t + step < 4 * a.tiles && L.first[t + step] <= tid) t += step;
+        const uint32_t at = t * kClassifyThreads;
+        L.point[tid] = w.eb[at + tid - L.first[t]] + (at << 13);
+    }
     if (tid == 0) L.s_bad = L.s_max = L.s_lastph = 0;
     __syncthreads();
     // The state after each point (a point per thread).
@@ -923,7 +931,7 @@ __device__ __forceinline__ void index_parallel(const BatchArgs &a, ParLds &L, ui
     uint64_t r = 0;
     if (live) {
         // Its issuer's last point before it, from the tile's last point back.
-        const uint32_t end = L.first[blockIdx.x + 1];
+        const uint32_t end = L.first[4 * (blockIdx.x + 1)];
         uint32_t at = kNone;
         for (uint32_t j = (end + 3) / 4; j > 0 && at == kNone; --j) {
             const vshmem_detail::v4u q = *(const vshmem_detail::v4u *)(L.point + 4 * (j - 1));
@@ -1014,25 +1022,36 @@ __global__ void __launch_bounds__(kIndexThreads) k_batch_index(BatchArgs a)
     if (a.tiles) {
         const uint32_t i = blockIdx.x * kParTile + threadIdx.x;
         const uint32_t cw = i < a.n ? a.w.key[i] : 0, nch = i < a.n ? a.w.nch[i] : 0;
-        // Points per tile, and whether the table qualifies.
+        // Points per list, and whether the table qualifies.
         if (threadIdx.x < 64) {
-            static_assert(kParTiles <= 64, "one lane per tile");
-            const uint32_t t = threadIdx.x, c = t < a.tiles ? a.w.maxf[t] : 0;
-            uint32_t sum = c & 0x7FFFFFFFu;
+            static_assert(kParLists == 4 * 64 && kParTile == 4 * kClassifyThreads, "four lists per lane and per tile");
+            const uint32_t t = threadIdx.x, nlists = (a.n + kClassifyThreads - 1) / kClassifyThreads;
+            uint32_t c[4], big = 0, mine = 0;
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) c[k] = 4 * t + k < nlists ? a.w.maxf[4 * t + k] : 0;
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                big |= c[k] >> 31;
+                mine += c[k] & 0x7FFFFFFFu;
+            }
+            uint32_t sum = mine;
 #pragma unroll
             for (int o = 1; o < 64; o <<= 1) {
                 const uint32_t y = __shfl_up(sum, o, 64);
                 if ((int)t >= o) sum += y;
             }
-            if (t < a.tiles) L.par.first[t + 1] = sum;
-            const bool big = __ballot(c >> 31) != 0;
-            if (t == 0) {
-                L.par.first[0] = 0;
-                L.par.s_big = big;
+            sum -= mine;
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                L.par.first[4 * t + k] = sum;
+                sum += c[k] & 0x7FFFFFFFu;
             }
+            if (t == 63) L.par.first[kParLists] = sum;
+            big = __ballot(big) != 0;
+            if (t == 0) L.par.s_big = big;
         }
         __syncthreads();
-        if (!rfl(L.par.s_big) && rfl(L.par.first[a.tiles]) <= kParSync) {
+        if (!rfl(L.par.s_big) && rfl(L.par.first[4 * a.tiles]) <= kParSync) {
             index_parallel(a, L.par, cw, nch);
             return;
         }
@@ -1099,7 +1118,7 @@ __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
     const Ws &w = a.w;
     const uint32_t active = rfl(w.ctl->active), last = rfl(w.ctl->last);
     if (blockIdx.x >= active) return;
-    if (threadIdx.x == 0) tune = *a.tune;
+    for (uint32_t k = threadIdx.x; k < sizeof(shmemx_tune_t) / 4; k += blockDim.x) ((uint32_t *)&tune)[k] = ((const uint32_t *)a.tune)[k];
     const bool lds = last <= kExecLdsPhases;
     const uint32_t bd = blockDim.x, waves = bd / 64, wave = threadIdx.x / 64;
     uint32_t staged = 0;   // phases whose first pack is in LDS
@@ -1259,7 +1278,7 @@ int launch_fused(const shmemx_desc_t *d_descs, size_t n, uint64_t *d_results, co
     a.results = d_results;
     a.w = ws_carve(ws, cap);
     const uint32_t ncls = (uint32_t)((n + kClassifyThreads - 1) / kClassifyThreads);
-    a.tiles = n <= kParTable ? ncls : 0;
+    a.tiles = n <= kParTable ? (uint32_t)((n + kParTile - 1) / kParTile) : 0;
     hipLaunchKernelGGL(k_batch_classify, dim3(ncls), dim3(kClassifyThreads), 0, stream, a);
     hipLaunchKernelGGL(k_batch_index, dim3(a.tiles ? a.tiles : 1), dim3(kIndexThreads), 0, stream, a);
     if (a.tiles) hipLaunchKernelGGL(k_batch_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, a);
