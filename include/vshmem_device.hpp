@@ -225,7 +225,8 @@ template <bool NT, typename T>
 __device__ __forceinline__ T ld_any(const uint8_t *p)
 {
     typedef T A __attribute__((aligned(1)));
-    return ld<NT>((const A *)p);
+    if constexpr (NT) return __builtin_nontemporal_load((const A *)p);
+    else return *(const A *)p;
 }
 
 template <bool NT, typename T>

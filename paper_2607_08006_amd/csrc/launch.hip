@@ -49,7 +49,7 @@ constexpr uint32_t kIndexTile = kIndexThreads * kIndexItems;
 // ordering points and no operation of kParTasks or more work-group tasks (so
 // that 32 bits hold any sum of tasks).  Otherwise one work-group builds it.
 constexpr uint32_t kParTile = kIndexThreads;
-constexpr uint32_t kParTable = 65536, kParTiles = kParTable / kParTile, kParLists = kParTable / kClassifyThreads;
+constexpr uint32_t kParTable = 65536, kParLists = kParTable / kClassifyThreads;
 constexpr uint32_t kParSync = 1024;
 constexpr uint32_t kParTasks = 65536;
 constexpr uint32_t kParBuckets = 8192;      // counters (packed count and tasks) in LDS and in memory
