@@ -936,8 +936,11 @@ __device__ __forceinline__ uint64_t member_stride(const shmem_dctx_t &ctx, const
 // Loads past the end read the last vector again, none under a condition of
 // its own (copy_vecs tells why): broadcast of 1 MiB to 64 members, chunks of
 // 64 KiB to four of them per task, 17.4 us through the loop of whole tiles
-// below, 16.2 so.  For few members, where the loads' latency counts: with 64
-// per task the loop is the faster one (16 MiB 178 us against 182).
+// below, 16.2 so.  For few members, where the loads' latency counts, and for
+// small work-groups and tasks, where the loop's sixteen conditions do (64
+// members, chunks of 8 KiB by 512 threads 78.6 us, 51.8 so; of 4 KiB by 64
+// threads 306 and 139): with 64 members per task and four vectors in each of
+// 1024 lanes the loop is the faster one (16 MiB 178 us against 182).
 template <bool NT, int T>
 __device__ __forceinline__ void mcast_small(uint8_t *d0, uint64_t pstride, int P, const uint8_t *s, uint32_t n,
                                             uint32_t worker)
@@ -988,7 +991,7 @@ __device__ __forceinline__ void multicast(uint8_t *d0, uint64_t pstride, int P, 
                 const uint64_t o = (q & 1) ? len - 16 : 0;
                 st_any<NT, v4u>(d0 + (q >> 1) * pstride + o, ld_any<true, v4u>(src + o));
             }
-    if (nv <= kMcastTile / 4 * bd && P <= 16) {
+    if (nv <= kMcastTile / 4 * bd && (P <= 16 || bd <= 512 || nv <= 2 * bd)) {
         if (nv) mcast_small<NT, kMcastTile / 4>(d0 + head, pstride, P, src + head, (uint32_t)nv, worker);
         return;
     }
@@ -1135,7 +1138,15 @@ __device__ __forceinline__ void pair_blocks(uint8_t *D0, const uint8_t *S0, uint
 
 // fcollect: blocks shorter than kPairMax go from each source to each
 // destination, many at once; longer ones are read once per group of members.
+// With fewer than eight wavefronts per member too few loads are in flight, and
+// a multicast's stores wait for none: 64 members, one wavefront each, 4 KiB
+// 36.2 us as pairs and 11.3; four each, 14.0 and 9.3 (10000 bytes 25.4 and
+// 12.8); eight each, 64 bytes 3.7 as pairs (four each, 7.9 as multicasts).
 constexpr uint64_t kPairMax = 16ull << 10;
+__host__ __device__ __forceinline__ bool use_pairs(uint64_t n, uint32_t P, uint32_t workers, uint32_t bd)
+{
+    return n < kPairMax && (uint64_t)workers * bd >= 512ull * P;
+}
 
 // TREE in streaming form.  Pushing x_0, x_1, ... keeps, for every set bit j
 // of the count, the reduction of an aligned block of 2^j consecutive inputs
@@ -1616,7 +1627,7 @@ __device__ __forceinline__ int shmemx_fcollectmem_grid(const shmem_dctx_t &ctx, 
         const uint32_t P = (uint32_t)team.size;
         uint8_t *D = vshmem_detail::member0(ctx, team, dest);
         const uint8_t *S = vshmem_detail::member0(ctx, team, src);
-        if (n < vshmem_detail::kPairMax)
+        if (vshmem_detail::use_pairs(n, P, W.n, blockDim.x))
             vshmem_detail::pair_blocks<false, 4, true>(
                 D, S, ps, P, n, W, vshmem_detail::pair_split<4>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk));
         else

@@ -203,7 +203,7 @@ int shmemx_fcollectmem_launch(shmem_team_t team, void *dest, const void *src, si
     if (rc || n == 0) return rc;
     const Coll k = g.coll();
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
-    if (n < vshmem_detail::kPairMax) {
+    if (vshmem_detail::use_pairs(n, k.P, grid, (uint32_t)L.wg_size)) {
         const vshmem_detail::PairSplit m = vshmem_detail::pair_split<4>(n, k.P, grid, (uint32_t)L.wg_size, g.chunk);
         return run(nt ? k_pairs<true, 4, true> : k_pairs<false, 4, true>, grid, L.wg_size, stream, k, m);
     }

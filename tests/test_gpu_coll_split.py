@@ -106,3 +106,29 @@ def test_reductions_split_over_wavefronts(npes, eighths):
                     oracle.reduce(ref, dt, oracle.RO_SUM, off, so, n)
                     assert np.array_equal(download(do + room), ref), (dt, nvec, to == src)
         assert_no_device_errors()
+
+
+@pytest.mark.parametrize("wgs,wg,chunk", [(1, 64, 4096), (7, 64, 0), (8, 64, 0), (1, 512, 8192), (1, 576, 32768)])
+@pytest.mark.parametrize("kind", ["broadcast", "fcollect"])
+def test_movement_with_few_wavefronts(kind, wgs, wg, chunk):
+    """Launches on both sides of eight wavefronts per member, and small
+    work-groups whose tasks are a few vectors per lane, for 17 members."""
+    npes = 17
+    with heap(npes, 4 << 20) as v:
+        src, dst = v.malloc(200064), v.malloc(npes * 200064 + 64)
+        so, do = v.offset(src), v.offset(dst)
+        launch = v.launch_cfg(wgs_per_pe=wgs, wg_size=wg, chunk_bytes=chunk)
+        for n in (7, 64, 4096, 16383, 16384, 32769, 200001):
+            init = W.heap_fill(0xFE, npes, do + npes * 200064 + 64)
+            for a, b in ((0, 0), (3, 5)):
+                upload(init)
+                ref = init.copy()
+                if kind == "broadcast":
+                    v.broadcastmem(dst + b, src + a, n, 3, launch=launch)
+                    ref[:, do + b:do + b + n] = init[3, so + a:so + a + n]
+                else:
+                    v.fcollectmem(dst + b, src + a, n, launch=launch)
+                    for q in range(npes):
+                        ref[:, do + b + q * n:do + b + (q + 1) * n] = init[q, so + a:so + a + n]
+                assert np.array_equal(download(init.shape[1]), ref), (n, a, b)
+        assert_no_device_errors()
