@@ -323,7 +323,7 @@ __device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__
     }
 }
 
-/* Copy n bytes with nl >= 2 cooperating lanes (this one is `lane`), at any
+/* Copy n bytes with nl cooperating lanes (this one is `lane`), at any
  * alignment of either side.  n >= 16: the destination's 16-byte vectors that
  * lie inside the message (stores stay aligned, loads take the source as it
  * falls), and the first and the last 16 bytes where the destination's edges
@@ -355,6 +355,7 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
     const uint64_t eo = lane + 1 == nl ? n - 16 : 0;
     const bool edge = lane + 1 == nl ? ((n - head) & 15) != 0 : lane + 2 == nl && head != 0;
     v4u e;
+    if (nl == 1 && head) st_any<NT, v4u>(d, ld_any<NT, v4u>(s));   // no second lane: `edge` is the last piece
     if (edge) e = ld_any<NT, v4u>(s + eo);
     copy_vecs<U, NT, AGAIN>((v4u *)(d + head), s + head, nv, lane, nl);
     if (edge) st_any<NT, v4u>(d + eo, e);

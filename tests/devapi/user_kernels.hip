@@ -222,6 +222,25 @@ __global__ void __launch_bounds__(256) k_user_debug(const shmemx_dctx_pub_t *pub
     }
 }
 
+// Put or get of one block between neighbours, from work-groups of any size:
+// `nwgs` work-groups act for each PE, with the _wg calls when that is one and
+// the _grid calls otherwise.
+__global__ void __launch_bounds__(256) k_user_move(const shmemx_dctx_pub_t *pub, int get, const uint8_t *src,
+                                                   uint8_t *dst, size_t n, int nwgs)
+{
+    const int pe = (int)(blockIdx.x / (unsigned)nwgs), rank = (int)blockIdx.x - pe * nwgs;
+    const shmem_dctx_t ctx = shmemx_dctx_bind(*pub, pe);
+    const int to = (pe + 1) % shmem_n_pes(ctx);
+    if (get) {
+        if (nwgs == 1) shmem_getmem_wg(ctx, dst, src, n, to);
+        else shmemx_getmem_grid(ctx, dst, src, n, to, rank, nwgs);
+    } else {
+        if (nwgs == 1) shmem_putmem_wg(ctx, dst, src, n, to);
+        else shmemx_putmem_grid(ctx, dst, src, n, to, rank, nwgs);
+    }
+    shmem_quiet_wg(ctx);
+}
+
 // A kernel that writes a descriptor table: record i is assembled from
 // column arrays (op, scope, aux and flags packed in one word per record).
 __global__ void k_user_write_table(shmemx_desc_t *out, size_t n, const uint32_t *code, const int32_t *issuer,
@@ -347,6 +366,15 @@ int usertest_debug(const void *dctx, const void *rec, const shmemx_dteam_t *pair
     if (!dctx || !rec || !pair || which < 0 || which > 6 || grid < 1 || grid > 2) return -1;
     hipLaunchKernelGGL(k_user_debug, dim3(grid), dim3(256), 0, (hipStream_t)stream, (const shmemx_dctx_pub_t *)dctx,
                        (const shmemx_dctx_rec_t *)rec, *pair, which, (uint8_t *)sym, (uint8_t *)outside, out);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int usertest_move(const void *dctx, int npes, int get, const void *src, void *dst, size_t n, int nwgs, int wg,
+                  void *stream)
+{
+    if (!dctx || npes < 1 || npes > 64 || nwgs < 1 || nwgs > 16 || wg < 1 || wg > 256) return -1;
+    hipLaunchKernelGGL(k_user_move, dim3(npes * nwgs), dim3(wg), 0, (hipStream_t)stream,
+                       (const shmemx_dctx_pub_t *)dctx, get, (const uint8_t *)src, (uint8_t *)dst, n, nwgs);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
