@@ -1097,7 +1097,7 @@ __device__ __forceinline__ void multicast_all(uint8_t *D, uint64_t ps, uint32_t 
 // lane), about eight to a wavefront where the blocks allow it, so that
 // wavefronts end together whatever the block size.  Blocks shorter than a
 // batch go to a group of g lanes, the smallest power of two that covers one
-// in a pass.  64 members, one 1024-thread work-group per CU: blocks of 300000
+// in a pass, at most a wavefront and never more than the work-group has.  64 members, one 1024-thread work-group per CU: blocks of 300000
 // bytes took 466 us cut into even chunks per work-group (whose last, partly
 // filled batch is a round trip of its own) and take 437, blocks of 100001
 // bytes 166 and 159, 1 MiB 1480 and 1460.  Consecutive tasks go to different work-groups first, so a few
@@ -1114,8 +1114,8 @@ __host__ __device__ __forceinline__ PairSplit pair_split(uint64_t n, uint32_t P,
     const uint64_t share = udiv(n * P * P, (uint64_t)workers * most(bd / 64, 1) * 8);
     PairSplit m;
     m.task = least(least(chunk, n), most(kBatch, least(share / kBatch * kBatch, 64u << 10)));
-    m.g = 2;
-    while (m.g < 64 && m.g * kPass < m.task) m.g <<= 1;
+    m.g = bd < 2 ? 1 : 2;
+    while (m.g < 64 && 2 * m.g <= bd && m.g * kPass < m.task) m.g <<= 1;
     m.nch = udiv(n + m.task - 1, m.task);
     return m;
 }

@@ -378,4 +378,37 @@ int usertest_move(const void *dctx, int npes, int get, const void *src, void *ds
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// As usertest_collective for the data-movement kinds, by work-groups of any
+// size from one thread on.
+int usertest_collective_any(const void *dctx, const shmemx_dteam_t *team, int kind, void *dest, const void *src,
+                            size_t n, int root, int nwgs, int wg, int *status, void *stream)
+{
+    if (!dctx || !team || kind < 0 || kind > KIND_ALLTOALL || nwgs < 1 || wg < 1 || wg > 256 || !status ||
+        team->size * nwgs > 256)
+        return -1;
+    const dim3 grid(team->size * nwgs), block(wg);
+    const auto *pub = (const shmemx_dctx_pub_t *)dctx;
+    hipStream_t s = (hipStream_t)stream;
+#define USER_LAUNCH(K) \
+    hipLaunchKernelGGL((k_user_collective<K, 0, 0>), grid, block, 0, s, pub, *team, dest, src, n, root, nwgs, status)
+    if (kind == KIND_BROADCAST) USER_LAUNCH(KIND_BROADCAST);
+    else if (kind == KIND_FCOLLECT) USER_LAUNCH(KIND_FCOLLECT);
+    else USER_LAUNCH(KIND_ALLTOALL);
+#undef USER_LAUNCH
+    return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// How the header cuts blocks of n bytes between pairs of P members for
+// `workers` work-groups of wg threads: bytes per task, tasks per block, lanes
+// per task.  Runs on the host.
+int usertest_pair_split(int deep, uint64_t n, uint32_t P, uint32_t workers, uint32_t wg, uint64_t chunk, uint64_t *out)
+{
+    const vshmem_detail::PairSplit m = deep ? vshmem_detail::pair_split<8>(n, P, workers, wg, chunk)
+                                            : vshmem_detail::pair_split<4>(n, P, workers, wg, chunk);
+    out[0] = m.task;
+    out[1] = m.nch;
+    out[2] = m.g;
+    return 0;
+}
+
 }  // extern "C"

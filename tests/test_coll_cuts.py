@@ -1,0 +1,32 @@
+"""How the header cuts the data-movement collectives into tasks: the functions
+run on the host, through the user-test library."""
+import ctypes
+import os
+
+import pytest
+
+LIB = os.path.join(os.path.dirname(os.path.abspath(__file__)), "devapi", "libvshmem_usertest.so")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not os.path.exists(LIB):
+        import __graft_entry__ as g
+        g.build()
+    import paper_2607_08006_amd  # noqa: F401  (torch's runtime first)
+    return ctypes.CDLL(LIB)
+
+
+@pytest.mark.parametrize("wg", [1, 2, 3, 16, 32, 48, 63, 64, 96, 256, 1024])
+def test_a_pair_task_fits_its_work_group(lib, wg):
+    """A task's lanes exist in the work-group, are a power of two, at most a
+    wavefront, and a block's tasks cover it."""
+    out = (ctypes.c_uint64 * 3)()
+    for deep in (0, 1):
+        for n in (1, 16, 1000, 2048, 2049, 4096, 4097, 16383, 16384, 100001, 1 << 20, 300 << 20):
+            for P, workers in ((1, 1), (3, 3), (13, 208), (64, 64), (64, 256), (500, 1000)):
+                for chunk in (16, 4112, 256 << 10):
+                    lib.usertest_pair_split(deep, ctypes.c_uint64(n), P, workers, wg, ctypes.c_uint64(chunk), out)
+                    task, nch, g = out
+                    assert 1 <= g <= min(wg, 64) and g & (g - 1) == 0, (n, P, workers, chunk)
+                    assert 0 < task <= chunk and (nch - 1) * task < n <= nch * task, (n, P, workers, chunk)
