@@ -241,6 +241,35 @@ __global__ void __launch_bounds__(256) k_user_move(const shmemx_dctx_pub_t *pub,
     shmem_quiet_wg(ctx);
 }
 
+// A list of puts or gets (source offset, destination offset, bytes), the PE's
+// own at one end and its right neighbour's at the other: one operation per
+// lane, wavefront or work-group.  One work-group per PE.
+__global__ void __launch_bounds__(256) k_user_moves(const shmemx_dctx_pub_t *pub, int scope, int get,
+                                                    const uint64_t *ops, int nops)
+{
+    const shmem_dctx_t ctx = shmemx_dctx_bind(*pub, (int)blockIdx.x);
+    const int to = ((int)blockIdx.x + 1) % shmem_n_pes(ctx);
+    uint8_t *base = ctx.c.base;
+    const int first = scope == SHMEMX_SCOPE_THREAD ? threadIdx.x : scope == SHMEMX_SCOPE_WAVE ? threadIdx.x / 64 : 0;
+    const int step = scope == SHMEMX_SCOPE_THREAD ? blockDim.x : scope == SHMEMX_SCOPE_WAVE ? blockDim.x / 64 : 1;
+    for (int k = first; k < nops; k += step) {
+        const uint8_t *src = base + ops[3 * k];
+        uint8_t *dst = base + ops[3 * k + 1];
+        const size_t n = ops[3 * k + 2];
+        if (scope == SHMEMX_SCOPE_THREAD) {
+            if (get) shmem_getmem(ctx, dst, src, n, to);
+            else shmem_putmem(ctx, dst, src, n, to);
+        } else if (scope == SHMEMX_SCOPE_WAVE) {
+            if (get) shmem_getmem_wave(ctx, dst, src, n, to);
+            else shmem_putmem_wave(ctx, dst, src, n, to);
+        } else {
+            if (get) shmem_getmem_wg(ctx, dst, src, n, to);
+            else shmem_putmem_wg(ctx, dst, src, n, to);
+        }
+    }
+    shmem_quiet_wg(ctx);
+}
+
 // A kernel that writes a descriptor table: record i is assembled from
 // column arrays (op, scope, aux and flags packed in one word per record).
 __global__ void k_user_write_table(shmemx_desc_t *out, size_t n, const uint32_t *code, const int32_t *issuer,
@@ -409,6 +438,17 @@ int usertest_pair_split(int deep, uint64_t n, uint32_t P, uint32_t workers, uint
     out[1] = m.nch;
     out[2] = m.g;
     return 0;
+}
+
+// ops: nops triples in device memory.
+int usertest_moves(const void *dctx, int npes, int scope, int get, const uint64_t *ops, int nops, int wg, void *stream)
+{
+    if (!dctx || npes < 1 || npes > 64 || scope < SHMEMX_SCOPE_THREAD || scope > SHMEMX_SCOPE_WG || !ops || nops < 0 ||
+        wg < 64 || wg > 256 || wg % 64)
+        return -1;
+    hipLaunchKernelGGL(k_user_moves, dim3(npes), dim3(wg), 0, (hipStream_t)stream, (const shmemx_dctx_pub_t *)dctx,
+                       scope, get, ops, nops);
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 }  // extern "C"

@@ -103,6 +103,7 @@ def user_lib():
         "usertest_debug": [vp, vp, vp, i32, vp, vp, vp, i32, vp],
         "usertest_move": [vp, i32, i32, vp, vp, sz, i32, i32, vp],
         "usertest_collective_any": [vp, vp, i32, vp, vp, sz, i32, i32, i32, vp, vp],
+        "usertest_moves": [vp, i32, i32, i32, vp, i32, i32, vp],
         "usertest_write_table": [vp, sz, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp],
     }
     for name, args in sigs.items():
