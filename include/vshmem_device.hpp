@@ -150,6 +150,13 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint64_t now() { return wall_clock64(); }
 
+__device__ __forceinline__ uint64_t first_lane64(uint64_t x)
+{
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
 __device__ __forceinline__ void latch_error(const shmemx_dctx_pub_t &c, uint32_t bits)
 {
     __hip_atomic_fetch_or(c.err, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -241,6 +248,18 @@ __device__ __forceinline__ void st_any(uint8_t *p, T v)
  * a load whose value only a conditional store uses into the condition. */
 __device__ __forceinline__ void loads_issued() { asm volatile("" ::: "memory"); }
 
+/* The same for loads through a __restrict__ pointer, which an asm statement
+ * that does not name them would not keep: all of them have arrived here. */
+template <int V>
+__device__ __forceinline__ void loaded(v4u (&r)[V])
+{
+    static_assert(V == 1 || V == 2 || V == 4 || V == 8, "");
+    if constexpr (V == 2) asm volatile("" : "+v"(r[0]), "+v"(r[1]));
+    if constexpr (V == 4) asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
+    if constexpr (V == 8)
+        asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
+}
+
 /* nv 16-byte vectors to an aligned destination by one lane: U at a time, then
  * half as many, down to one. */
 template <int U, bool NT>
@@ -298,46 +317,34 @@ __device__ __forceinline__ void copy_lone(uint8_t *__restrict__ d, const uint8_t
     }
 }
 
-/* nv 16-byte vectors to an aligned destination from a source at any address,
- * by nl lanes (this one is `lane`), U loads in flight per lane, also in the
- * last, partly filled batch.  AGAIN: a lane's loads past the end read the
- * last vector again, none under a condition of its own.  In the batches'
- * executors the compiler put a wait after each conditional load, a round trip
- * per vector (the 4-PE mixed program as a plan 34.8 us, and 32.6 with AGAIN);
- * in the copy kernels it does not, and the repeated loads cost up to 8%. */
-template <int U, bool NT, bool AGAIN = false>
-__device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__restrict__ s, uint64_t nv,
-                                          uint64_t lane, uint64_t nl)
+/* Pieces 0 .. np - 1 of 16 bytes by nl lanes, V in flight per lane (of whole
+ * wavefronts: each takes one contiguous run): piece k at 16 k, at most at
+ * `last` (which may lie before 0), and piece np - 1 at `end`.  np is at most
+ * V nl, and one more with MORE, which lane 0 takes.  Lanes past the end load
+ * a piece again and no load is under a condition of its own: after a
+ * conditional load the compiler puts a wait, a round trip for each. */
+template <int V, bool NT, bool MORE>
+__device__ __forceinline__ void copy_pieces(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t np,
+                                            int64_t last, int64_t end, uint64_t lane, uint64_t nl)
 {
-    // Full batches: a wavefront's U vectors per lane are one contiguous run
-    // (whole wavefronts; other lane counts take every nl-th vector).  With a
-    // source that is not on a boundary each wavefront then reads its lines
-    // once, but for the last: 64 KiB messages at odd addresses by 1024
-    // threads moved at 5.6 TB/s, and at 4.6 with every nl-th vector.
     const bool waves = (nl & 63) == 0;
-    const uint64_t w = waves ? 64 : nl;
-    const uint64_t first = waves ? (lane >> 6) * (U * 64) + (lane & 63) : lane;
-    uint64_t nb = 0;
-    for (; nb + U * nl <= nv; nb += U * nl) {
-        const uint64_t i = nb + first;
-        v4u r[U];
+    const uint64_t w = waves ? 64 : nl, k = waves ? (lane >> 6) * (V * 64) + (lane & 63) : lane;
+    if (k >= np) return;
+    int64_t o[V];
+    v4u r[V], x;
 #pragma unroll
-        for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + 16 * (i + u * w));
-#pragma unroll
-        for (int u = 0; u < U; ++u) st<NT>(d + i + u * w, r[u]);
+    for (int v = 0; v < V; ++v) {
+        const uint64_t q = k + v * w;
+        o[v] = q + 1 >= np ? end : min((int64_t)(16 * q), last);
+        r[v] = ld_any<NT, v4u>(s + o[v]);
     }
-    // The rest, in one batch.
-    const uint64_t i = nb + lane;
-    if (i < nv) {
-        v4u r[U];
+    const bool more = MORE && np > V * nl;
+    if (more) x = ld_any<NT, v4u>(s + end);
+    loaded(r);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (AGAIN || i + u * nl < nv) r[u] = ld_any<NT, v4u>(s + 16 * (AGAIN ? min(i + u * nl, nv - 1) : i + u * nl));
-        if (AGAIN) loads_issued();
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (i + u * nl < nv) st<NT>(d + i + u * nl, r[u]);
-    }
+    for (int v = 0; v < V; ++v)
+        if (v == 0 || k + v * w < np) st_any<NT, v4u>(d + o[v], r[v]);
+    if (more && lane == 0) st_any<NT, v4u>(d + end, x);
 }
 
 /* Copy n bytes with nl cooperating lanes (this one is `lane`), at any
@@ -347,14 +354,19 @@ __device__ __forceinline__ void copy_vecs(v4u *__restrict__ d, const uint8_t *__
  * are not on a boundary; those overlap the vectors beside them and write the
  * same bytes.  LONE marks a copy by one lane (lane 0 of 1).
  *
- * Bound by HBM for large messages and by that round trip for short ones.
- * Measured with one wavefront per message, one message at a time, 64 PEs,
- * 4096 messages per PE, U = 4: messages of 1501 bytes at addresses that
- * disagree modulo 16 moved at 2.6 TB/s, against 0.44 with the narrower
- * elements (down to bytes) that such a pair took before.  16 MiB messages by
- * 1024 threads, aligned, U = 8: 6.1 TB/s, against 5.7 with every nl-th
- * vector instead of contiguous runs per wavefront. */
-template <int U, bool NT, bool LONE = false, bool AGAIN = false>
+ * Bound by HBM for large messages, by a round trip and the instructions around
+ * it for short ones: so one piece per lane where the lanes suffice, whatever
+ * the alignment, and no loop.  A user's kernel putting one message after
+ * another, 4096 per PE, 64 PEs x 4 work-groups of 256: by wavefronts 64 bytes
+ * 92 us, where edges of their own and a conditional load per vector took 145;
+ * 1501 bytes at odd addresses 288; by work-groups 16 bytes 334 (515), 1 KiB 645
+ * (857).  With one wavefront per message, one message at a time, 1501 bytes at
+ * addresses that disagree modulo 16 moved at 2.6 TB/s, against 0.44 with
+ * elements down to bytes.  16 MiB messages by 1024 threads, aligned, U = 8:
+ * 6.1 TB/s, against 5.7 with every nl-th vector instead of contiguous runs per
+ * wavefront.  What is left behind aligned vectors joined by funnel shifts:
+ * sources off a boundary, 16 and 32 KiB by 1024 threads, 247 us and 217. */
+template <int U, bool NT, bool LONE = false>
 __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n,
                                            uint64_t lane, uint64_t nl)
 {
@@ -366,16 +378,49 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
         for (uint64_t i = lane; i < n; i += nl) d[i] = s[i];
         return;
     }
-    const uint64_t head = (16 - ((uintptr_t)d & 15)) & 15;
-    const uint64_t nv = (n - head) / 16;
-    // The edges, by the lanes that a short message leaves idle.
-    const uint64_t eo = lane + 1 == nl ? n - 16 : 0;
-    const bool edge = lane + 1 == nl ? ((n - head) & 15) != 0 : lane + 2 == nl && head != 0;
-    v4u e;
-    if (nl == 1 && head) st_any<NT, v4u>(d, ld_any<NT, v4u>(s));   // no second lane: `edge` is the last piece
-    if (edge) e = ld_any<NT, v4u>(s + eo);
-    copy_vecs<U, NT, AGAIN>((v4u *)(d + head), s + head, nv, lane, nl);
-    if (edge) st_any<NT, v4u>(d + eo, e);
+    // The destination's vectors that hold bytes of the message, moved inward
+    // to lie inside it: one piece per lane where the lanes suffice.
+    const uint64_t mis = (uintptr_t)d & 15, np = (mis + n + 15) >> 4;
+    if (np <= nl) {
+        if (lane < np) {
+            const uint64_t o = min(lane ? 16 * lane - mis : 0, n - 16);
+            st_any<NT, v4u>(d + o, ld_any<NT, v4u>(s + o));
+        }
+        return;
+    }
+    const uint64_t head = (16 - mis) & 15, nv = (n - head) / 16;
+    // Full batches: a wavefront's U vectors per lane are one contiguous run
+    // (whole wavefronts; other lane counts take every nl-th vector).  With a
+    // source that is not on a boundary each wavefront then reads its lines
+    // once, but for the last: 64 KiB messages at odd addresses by 1024
+    // threads moved at 5.6 TB/s, and at 4.6 with every nl-th vector.
+    const bool waves = (nl & 63) == 0;
+    const uint64_t w = waves ? 64 : nl;
+    const uint64_t first = waves ? (lane >> 6) * (U * 64) + (lane & 63) : lane;
+    v4u *dv = (v4u *)(d + head);
+    const uint8_t *sv = s + head;
+    uint64_t nb = 0;
+    for (; nb + U * nl <= nv; nb += U * nl) {
+        const uint64_t i = nb + first;
+        v4u r[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(sv + 16 * (i + u * w));
+#pragma unroll
+        for (int u = 0; u < U; ++u) st<NT>(dv + i + u * w, r[u]);
+    }
+    // The rest, in one round trip: the vectors past the batches, the last 16
+    // bytes if the end is off a boundary, and as the last piece the first 16
+    // bytes if the start is.
+    const uint64_t rest = np - nb;
+    if (rest == 0) return;
+    const uint64_t at = head + 16 * nb;
+    const int64_t last = (int64_t)(n - 16 - at), end = head ? -(int64_t)at : last;
+    d += at;
+    s += at;
+    if (U > 1 && rest <= nl) copy_pieces<1, NT, false>(d, s, rest, last, end, lane, nl);
+    else if (U > 2 && rest <= 2 * nl) copy_pieces<2, NT, false>(d, s, rest, last, end, lane, nl);
+    else if (U > 4 && rest <= 4 * nl) copy_pieces<4, NT, false>(d, s, rest, last, end, lane, nl);
+    else copy_pieces<U, NT, true>(d, s, rest, last, end, lane, nl);
 }
 
 __device__ __forceinline__ bool cmp_holds_u(uint64_t x, int cmp, uint64_t v)
@@ -479,13 +524,6 @@ __device__ __forceinline__ void counter_barrier(const shmemx_dctx_pub_t &c, uint
  * participant of a scoped call takes the same decision).  Without debug the
  * checks reduce to one uniform branch. */
 namespace vshmem_detail {
-
-__device__ __forceinline__ uint64_t first_lane64(uint64_t x)
-{
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
 
 __device__ __forceinline__ bool in_user_heap(const shmem_dctx_t &ctx, const void *p, uint64_t n)
 {
@@ -952,7 +990,7 @@ __device__ __forceinline__ uint64_t member_stride(const shmem_dctx_t &ctx, const
 // A multicast of n <= T * blockDim.x vectors, loaded once, then written to
 // one member after another, starting at a member that depends on the worker.
 // Loads past the end read the last vector again, none under a condition of
-// its own (copy_vecs tells why): broadcast of 1 MiB to 64 members, chunks of
+// its own (copy_pieces tells why): broadcast of 1 MiB to 64 members, chunks of
 // 64 KiB to four of them per task, 17.4 us through the loop of whole tiles
 // below, 16.2 so.  For few members, where the loads' latency counts, and for
 // small work-groups and tasks, where the loop's sixteen conditions do (64

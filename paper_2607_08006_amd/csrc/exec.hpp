@@ -90,9 +90,13 @@ __device__ __forceinline__ void exec_copy(const shmemx_dctx_pub_t &c, const shme
     const bool get = d.op == SHMEMX_OP_GET;
     const int spe = get ? d.target_pe : d.issuer_pe;
     const int dpe = get ? d.issuer_pe : d.target_pe;
-    const uint8_t *S = c.base + (uint64_t)spe * c.stride + d.src + lo;
-    uint8_t *D = c.base + (uint64_t)dpe * c.stride + d.dst + lo;
-    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, LONE, true>(D, S, hi - lo, lane, nl);
+    uint64_t so = (uint64_t)spe * c.stride + d.src + lo, to = (uint64_t)dpe * c.stride + d.dst + lo, n = hi - lo;
+    if (!LONE) {   // one descriptor per wavefront: its fields belong in scalar registers
+        so = vshmem_detail::first_lane64(so);
+        to = vshmem_detail::first_lane64(to);
+        n = vshmem_detail::first_lane64(n);
+    }
+    vshmem_detail::copy_bytes<VSHMEM_COPY_UNROLL, false, LONE>(c.base + to, c.base + so, n, lane, nl);
 }
 
 __device__ __forceinline__ void signal_of(const shmemx_dctx_pub_t &c, const shmemx_desc_t &d)
