@@ -1152,14 +1152,22 @@ __device__ __forceinline__ void multicast_all(uint8_t *D, uint64_t ps, uint32_t 
 // lane), about eight to a wavefront where the blocks allow it, so that
 // wavefronts end together whatever the block size.  Blocks shorter than a
 // batch go to a group of g lanes, the smallest power of two that covers one
-// in a pass, at most a wavefront and never more than the work-group has.  64 members, one 1024-thread work-group per CU: blocks of 300000
-// bytes took 466 us cut into even chunks per work-group (whose last, partly
-// filled batch is a round trip of its own) and take 437, blocks of 100001
-// bytes 166 and 159, 1 MiB 1480 and 1460.  Consecutive tasks go to different work-groups first, so a few
-// tiny blocks per member still spread over every work-group.
+// in a pass, at most a wavefront and never more than the work-group has.
+// Consecutive tasks go to different work-groups first, so a few tiny blocks
+// per member still spread over every work-group.
+//
+// 64 members, one 1024-thread work-group per CU: blocks of 300000 bytes took
+// 466 us cut into even chunks per work-group (whose last, partly filled batch
+// is a round trip of its own) and take 437, blocks of 100001 bytes 166 and 159,
+// 1 MiB 1480 and 1460.  Few wavefronts feel each task: where a wavefront has
+// eight blocks or more they stay whole (a task is two more pages to translate:
+// 64 members, one wavefront each, 100000 bytes 719 us in two tasks per block,
+// 575 in one), and a unit steps from task to task without a division.
 struct PairSplit {
     uint64_t task, nch;   // bytes per task, tasks per block
-    uint32_t g;           // lanes per task
+    uint64_t schunk;      // a unit's next task: this many further in its block,
+    uint32_t sq, sp;      // source members and destination members
+    uint32_t g, pad;      // lanes per task
 };
 template <int U>
 __host__ __device__ __forceinline__ PairSplit pair_split(uint64_t n, uint32_t P, uint32_t workers, uint32_t bd, uint64_t chunk)
@@ -1168,27 +1176,60 @@ __host__ __device__ __forceinline__ PairSplit pair_split(uint64_t n, uint32_t P,
     // (Work-groups below a wavefront count as one.)
     const uint64_t share = udiv(n * P * P, (uint64_t)workers * most(bd / 64, 1) * 8);
     PairSplit m;
-    m.task = least(least(chunk, n), most(kBatch, least(share / kBatch * kBatch, 64u << 10)));
+    // Split for balance, but where a unit has eight blocks or more; even then
+    // in equal tasks, no larger than a chunk.
+    const uint64_t parts = udiv(n + chunk - 1, chunk), even = (udiv(n + parts - 1, parts) + kBatch - 1) / kBatch * kBatch;
+    m.task = least(least(chunk, n), share >= n ? even : most(kBatch, least(share / kBatch * kBatch, 64u << 10)));
     m.g = bd < 2 ? 1 : 2;
     while (m.g < 64 && 2 * m.g <= bd && m.g * kPass < m.task) m.g <<= 1;
+    m.pad = 0;
     m.nch = udiv(n + m.task - 1, m.task);
+    const uint64_t step = (uint64_t)workers * (bd / m.g), blocks = udiv(step, m.nch);
+    m.schunk = step - blocks * m.nch;
+    m.sp = (uint32_t)udiv(blocks, P);
+    m.sq = (uint32_t)(blocks - (uint64_t)m.sp * P);
     return m;
+}
+// Unit `unit` (of W.n * groups) takes tasks unit, unit + W.n * groups, ...
+template <bool NT, int U, bool ONE>
+__device__ __forceinline__ void pair_tasks(uint8_t *D0, const uint8_t *S0, uint64_t ps, uint32_t P, uint64_t n,
+                                           uint64_t unit, uint64_t lane, uint64_t nl, const PairSplit &m)
+{
+    const uint64_t blk = m.nch == 1 ? unit : udiv(unit, m.nch);
+    uint64_t c = unit - blk * m.nch;                       // chunk of the block
+    uint64_t p = udiv(blk, P);                             // destination member
+    uint32_t q = (uint32_t)(blk - p * P);                  // source member
+    while (p < P) {
+        const uint64_t off = c * m.task;
+        copy_bytes<U, NT>(D0 + p * ps + q * n + off, S0 + q * ps + (ONE ? 0 : p * n) + off, min(m.task, n - off),
+                          lane, nl);
+        c += m.schunk;
+        q += m.sq;
+        p += m.sp;
+        if (c >= m.nch) {
+            c -= m.nch;
+            ++q;
+        }
+        if (q >= P) {
+            q -= P;
+            ++p;
+        }
+    }
 }
 template <bool NT, int U, bool ONE>
 __device__ __forceinline__ void pair_blocks(uint8_t *D0, const uint8_t *S0, uint64_t ps, uint32_t P, uint64_t n,
                                             const Workers &W, const PairSplit &m)
 {
-    const uint64_t task = m.task, nch = m.nch, ntask = nch * P * P;
     const uint32_t g = m.g;
-    const uint32_t mine = threadIdx.x / g, lane = threadIdx.x % g, groups = blockDim.x / g;
-    if (mine >= groups) return;   // threads past the last whole group
-    for (uint64_t t = (uint64_t)mine * W.n + W.w; t < ntask; t += (uint64_t)W.n * groups) {
-        const uint64_t blk = udiv(t, nch);
-        const uint32_t p = (uint32_t)udiv(blk, P);              // destination member
-        const uint32_t q = (uint32_t)(blk - (uint64_t)p * P);   // source member
-        const uint64_t off = (t - blk * nch) * task;
-        copy_bytes<U, NT>(D0 + p * ps + q * n + off, S0 + q * ps + (ONE ? 0 : p * n) + off, min(task, n - off), lane,
-                          g);
+    if (g == 64) {
+        // A wavefront's tasks: their places stay in scalar registers.
+        const uint32_t mine = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        if ((mine + 1) * 64 <= blockDim.x)
+            pair_tasks<NT, U, ONE>(D0, S0, ps, P, n, (uint64_t)mine * W.n + W.w, threadIdx.x & 63, 64, m);
+    } else {
+        const uint32_t mine = threadIdx.x >> __builtin_ctz(g);
+        if ((mine + 1) * g <= blockDim.x)   // not past the last whole group
+            pair_tasks<NT, U, ONE>(D0, S0, ps, P, n, (uint64_t)mine * W.n + W.w, threadIdx.x & (g - 1), g, m);
     }
 }
 

@@ -429,7 +429,8 @@ int usertest_collective_any(const void *dctx, const shmemx_dteam_t *team, int ki
 
 // How the header cuts blocks of n bytes between pairs of P members for
 // `workers` work-groups of wg threads: bytes per task, tasks per block, lanes
-// per task.  Runs on the host.
+// per task, and the step from a unit's task to its next in chunks, source and
+// destination members.  Runs on the host.
 int usertest_pair_split(int deep, uint64_t n, uint32_t P, uint32_t workers, uint32_t wg, uint64_t chunk, uint64_t *out)
 {
     const vshmem_detail::PairSplit m = deep ? vshmem_detail::pair_split<8>(n, P, workers, wg, chunk)
@@ -437,6 +438,9 @@ int usertest_pair_split(int deep, uint64_t n, uint32_t P, uint32_t workers, uint
     out[0] = m.task;
     out[1] = m.nch;
     out[2] = m.g;
+    out[3] = m.schunk;
+    out[4] = m.sq;
+    out[5] = m.sp;
     return 0;
 }
 

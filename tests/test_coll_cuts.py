@@ -20,13 +20,27 @@ def lib():
 @pytest.mark.parametrize("wg", [1, 2, 3, 16, 32, 48, 63, 64, 96, 256, 1024])
 def test_a_pair_task_fits_its_work_group(lib, wg):
     """A task's lanes exist in the work-group, are a power of two, at most a
-    wavefront, and a block's tasks cover it."""
-    out = (ctypes.c_uint64 * 3)()
+    wavefront, a block's tasks cover it, and a unit's step passes over one task
+    of every other unit."""
+    out = (ctypes.c_uint64 * 6)()
     for deep in (0, 1):
         for n in (1, 16, 1000, 2048, 2049, 4096, 4097, 16383, 16384, 100001, 1 << 20, 300 << 20):
             for P, workers in ((1, 1), (3, 3), (13, 208), (64, 64), (64, 256), (500, 1000)):
                 for chunk in (16, 4112, 256 << 10):
                     lib.usertest_pair_split(deep, ctypes.c_uint64(n), P, workers, wg, ctypes.c_uint64(chunk), out)
-                    task, nch, g = out
+                    task, nch, g, schunk, sq, sp = out
                     assert 1 <= g <= min(wg, 64) and g & (g - 1) == 0, (n, P, workers, chunk)
                     assert 0 < task <= chunk and (nch - 1) * task < n <= nch * task, (n, P, workers, chunk)
+                    assert schunk < nch and sq < P
+                    assert schunk + nch * (sq + P * sp) == workers * (wg // g), (n, P, workers, chunk)
+
+
+@pytest.mark.parametrize("n", [100000, 262144, 300000, 1 << 20])
+def test_blocks_stay_whole_where_units_have_many(lib, n):
+    """With eight blocks or more per wavefront a block is cut only by the chunk
+    size, into equal tasks."""
+    out = (ctypes.c_uint64 * 6)()
+    for P, workers, wg in ((64, 64, 64), (64, 64, 256), (64, 128, 256), (16, 16, 64)):
+        lib.usertest_pair_split(1, ctypes.c_uint64(n), P, workers, wg, ctypes.c_uint64(256 << 10), out)
+        parts = -(-n // (256 << 10))
+        assert out[1] == parts and out[0] - (n - (parts - 1) * out[0]) < parts * 8192, (P, workers, wg, out[0])
