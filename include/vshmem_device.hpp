@@ -494,21 +494,27 @@ __device__ __forceinline__ uint64_t *sync_slot(const shmemx_dctx_pub_t &c, int p
  * work-group's wavefronts share.  With the generation word on a line of
  * its own a 64-PE barrier took 3.2 us instead of 5.9, a 256-PE one 9.5
  * instead of 21.5 (waiters' polls no longer queue with the arrivals'
- * atomics). */
-__device__ __forceinline__ void counter_barrier(const shmemx_dctx_pub_t &c, uint64_t *slot, uint64_t units)
+ * atomics).  `meanwhile` runs between the arrival and the wait. */
+struct Nothing {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <class F = Nothing>
+__device__ __forceinline__ void counter_barrier(const shmemx_dctx_pub_t &c, uint64_t *slot, uint64_t units,
+                                                F meanwhile = F())
 {
     uint64_t *cnt = slot;
     uint64_t *gen = (uint64_t *)((uint8_t *)slot + VSHMEM_SYNC_GEN_OFF);
     release_agent();
     const uint64_t old = __hip_atomic_fetch_add(cnt, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const uint64_t next = (uint64_t)((uint32_t)(old >> 32) + 1u);
-    if ((old & 0xffffffffull) == units - 1) {
+    const bool last = (old & 0xffffffffull) == units - 1;
+    if (last) {
         acquire_agent();   // the other arrivals' releases
         __hip_atomic_store(cnt, next << 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(gen, next, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        spin_until<false>(c, gen, 0 /*EQ*/, next);
     }
+    meanwhile();
+    if (!last) spin_until<false>(c, gen, 0 /*EQ*/, next);
     acquire_agent();
 }
 
@@ -977,6 +983,33 @@ __device__ __forceinline__ Workers team_workers(const shmem_dctx_t &ctx, const s
     return Workers{k * (uint32_t)nwgs + (uint32_t)rank, (uint32_t)team.size * (uint32_t)nwgs};
 }
 
+// The team barrier that opens a collective; thread 0 computes how the work is
+// cut, cut(), between its arrival and its wait, and the others get it through
+// LDS: the divisions, four wavefronts of a SIMD taking turns at them, cost a
+// broadcast of 64 bytes to 4 members by 1024 threads each 1.2 of its 6.5 us.
+template <class F>
+__device__ __forceinline__ auto open_collective(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, int nwgs, F cut)
+{
+    using T = decltype(cut());
+    constexpr int N = sizeof(T) / 8;
+    static_assert(sizeof(T) == 8 * N, "whole 64-bit words");
+    __shared__ uint64_t words[N];
+    wait_vm_complete();
+    __syncthreads();
+    if (threadIdx.x == 0)
+        counter_barrier(ctx.c, sync_slot(ctx.c, team.start, team.slot), (uint64_t)team.size * (uint64_t)nwgs, [&] {
+            const T m = cut();
+            __builtin_memcpy(words, &m, sizeof(T));
+        });
+    __syncthreads();
+    uint64_t u[N];
+    T m;
+#pragma unroll
+    for (int i = 0; i < N; ++i) u[i] = first_lane64(words[i]);
+    __builtin_memcpy(&m, u, sizeof(T));
+    return m;
+}
+
 // Member 0's copy of a symmetric object, and the distance between members.
 __device__ __forceinline__ uint8_t *member0(const shmem_dctx_t &ctx, const shmemx_dteam_t &team, const void *sym)
 {
@@ -1002,6 +1035,7 @@ __device__ __forceinline__ void mcast_small(uint8_t *d0, uint64_t pstride, int P
                                             uint32_t worker)
 {
     const uint32_t i = threadIdx.x, bd = blockDim.x;
+    if (i >= n) return;   // wavefronts without a vector load none
     v4u r[T];
 #pragma unroll
     for (int u = 0; u < T; ++u) r[u] = ld_any<true, v4u>(s + 16u * min(i + u * bd, n - 1));
@@ -1047,7 +1081,7 @@ __device__ __forceinline__ void multicast(uint8_t *d0, uint64_t pstride, int P, 
                 const uint64_t o = (q & 1) ? len - 16 : 0;
                 st_any<NT, v4u>(d0 + (q >> 1) * pstride + o, ld_any<true, v4u>(src + o));
             }
-    if (nv <= kMcastTile / 4 * bd && (P <= 16 || bd <= 512 || nv <= 2 * bd)) {
+    if (nv <= kMcastTile / 4 * bd && (P <= 16 || bd <= 512 || nv <= bd)) {
         if (nv) mcast_small<NT, kMcastTile / 4>(d0 + head, pstride, P, src + head, (uint32_t)nv, worker);
         return;
     }
@@ -1137,7 +1171,7 @@ __device__ __forceinline__ void multicast_all(uint8_t *D, uint64_t ps, uint32_t 
 {
     const uint64_t ntask = m.nch * Q * m.groups;
     for (uint64_t t = W.w; t < ntask; t += W.n) {
-        const uint64_t r = udiv(t, m.nch), g = udiv(r, Q), q = r - g * Q;
+        const uint64_t r = m.nch == 1 ? t : udiv(t, m.nch), g = Q == 1 ? r : udiv(r, Q), q = r - g * Q;
         const uint64_t off = (t - r * m.nch) * m.chunk;
         const uint32_t p0 = (uint32_t)g * m.per;
         multicast<NT>(D + p0 * ps + q * n + off, ps, (int)min(m.per, P - p0), src + q * sstep + off,
@@ -1694,14 +1728,16 @@ __device__ __forceinline__ int shmemx_broadcastmem_grid(const shmem_dctx_t &ctx,
     if (!vshmem_detail::coll_ok(ctx, team, dest, n, src, n, root >= 0 && root < team.size && rank >= 0 && rank < nwgs,
                                 n, ((uint64_t)(uint32_t)nwgs << 32) | (uint32_t)root))
         return SHMEMX_ERR_ARG;
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
+    const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
+    const uint32_t P = (uint32_t)team.size;
+    const vshmem_detail::McastSplit m = vshmem_detail::open_collective(ctx, team, nwgs, [&] {
+        return n ? vshmem_detail::mcast_split(n, 1, P, W.n, vshmem_detail::kCollChunk) : vshmem_detail::McastSplit{};
+    });
     if (n) {
-        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
         const uint64_t ps = vshmem_detail::member_stride(ctx, team);
-        const uint32_t P = (uint32_t)team.size;
         vshmem_detail::multicast_all<false>(vshmem_detail::member0(ctx, team, dest), ps, P,
                                             vshmem_detail::member0(ctx, team, src) + (uint64_t)root * ps, 0, 1, n, W,
-                                            vshmem_detail::mcast_split(n, 1, P, W.n, vshmem_detail::kCollChunk));
+                                            m);
     }
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
@@ -1717,19 +1753,25 @@ __device__ __forceinline__ int shmemx_fcollectmem_grid(const shmem_dctx_t &ctx, 
     if (!vshmem_detail::coll_ok(ctx, team, dest, (uint64_t)n * team.size, src, n, rank >= 0 && rank < nwgs, n,
                                 (uint64_t)nwgs))
         return SHMEMX_ERR_ARG;
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
+    const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
+    const uint32_t P = (uint32_t)team.size;
+    const bool pairs = vshmem_detail::use_pairs(n, P, W.n, blockDim.x);
+    struct Cut {
+        vshmem_detail::McastSplit m;
+        vshmem_detail::PairSplit p;
+    };
+    const Cut cut = vshmem_detail::open_collective(ctx, team, nwgs, [&] {
+        Cut c = {};
+        if (n && pairs) c.p = vshmem_detail::pair_split<4>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk);
+        else if (n) c.m = vshmem_detail::mcast_split(n, P, P, W.n, vshmem_detail::kCollChunk);
+        return c;
+    });
     if (n) {
-        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
         const uint64_t ps = vshmem_detail::member_stride(ctx, team);
-        const uint32_t P = (uint32_t)team.size;
         uint8_t *D = vshmem_detail::member0(ctx, team, dest);
         const uint8_t *S = vshmem_detail::member0(ctx, team, src);
-        if (vshmem_detail::use_pairs(n, P, W.n, blockDim.x))
-            vshmem_detail::pair_blocks<false, 4, true>(
-                D, S, ps, P, n, W, vshmem_detail::pair_split<4>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk));
-        else
-            vshmem_detail::multicast_all<false>(D, ps, P, S, ps, P, n, W,
-                                                vshmem_detail::mcast_split(n, P, P, W.n, vshmem_detail::kCollChunk));
+        if (pairs) vshmem_detail::pair_blocks<false, 4, true>(D, S, ps, P, n, W, cut.p);
+        else vshmem_detail::multicast_all<false>(D, ps, P, S, ps, P, n, W, cut.m);
     }
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
@@ -1745,15 +1787,16 @@ __device__ __forceinline__ int shmemx_alltoallmem_grid(const shmem_dctx_t &ctx, 
     if (!vshmem_detail::coll_ok(ctx, team, dest, (uint64_t)n * team.size, src, (uint64_t)n * team.size,
                                 rank >= 0 && rank < nwgs, n, (uint64_t)nwgs))
         return SHMEMX_ERR_ARG;
-    shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
-    if (n) {
-        const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
-        const uint32_t P = (uint32_t)team.size;
+    const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);
+    const uint32_t P = (uint32_t)team.size;
+    const vshmem_detail::PairSplit m = vshmem_detail::open_collective(ctx, team, nwgs, [&] {
+        return n ? vshmem_detail::pair_split<8>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk)
+                 : vshmem_detail::PairSplit{};
+    });
+    if (n)
         vshmem_detail::pair_blocks<true, 8, false>(
             vshmem_detail::member0(ctx, team, dest), vshmem_detail::member0(ctx, team, src),
-            vshmem_detail::member_stride(ctx, team), P, n, W,
-            vshmem_detail::pair_split<8>(n, P, W.n, blockDim.x, vshmem_detail::kCollChunk));
-    }
+            vshmem_detail::member_stride(ctx, team), P, n, W, m);
     shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);
     return 0;
 }
@@ -1772,12 +1815,14 @@ __device__ __forceinline__ int shmem_alltoallmem_wg(const shmem_dctx_t &ctx, con
                                     rank >= 0 && rank < nwgs, nreduce, (uint64_t)nwgs))                            \
             return SHMEMX_ERR_ARG;                                                                                 \
         if (team.size >= (1 << vshmem_detail::kTreeLevels)) return SHMEMX_ERR_UNSUPPORTED;                         \
-        shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);                                                         \
         const vshmem_detail::Workers W = vshmem_detail::team_workers(ctx, team, rank, nwgs);                      \
         uint8_t *D = vshmem_detail::member0(ctx, team, dest);                                                      \
+        const vshmem_detail::RedSplit m = vshmem_detail::open_collective(ctx, team, nwgs, [&] {                    \
+            return vshmem_detail::red_split(D, nreduce, sizeof(T), W.n, vshmem_detail::kRedChunk);                 \
+        });                                                                                                        \
         vshmem_detail::reduce<vshmem_detail::CODEC, vshmem_detail::OP, true>(                                      \
             D, vshmem_detail::member0(ctx, team, src), vshmem_detail::member_stride(ctx, team), team.size, nreduce, \
-            W, vshmem_detail::red_split(D, nreduce, sizeof(T), W.n, vshmem_detail::kRedChunk));                    \
+            W, m);                                                                                                 \
         shmemx_team_sync_units(ctx, team, (uint64_t)nwgs);                                                         \
         return 0;                                                                                                  \
     }
