@@ -59,12 +59,13 @@ __device__ __forceinline__ void stamp(uint64_t *stamps, uint64_t idx)
 // kStageDescs is four wavefronts' worth for 16 phases: at 5 KB the stage does
 // not limit how many small work-groups a CU holds.
 constexpr int kStagePhases = 16, kStageDescs = 64;
-struct PlanStage {
+struct __align__(16) PlanStage {
     uint32_t first[kStagePhases + 1];   // task offsets of the phases
     uint32_t pad[3];
     PlanTask task[kStagePhases];
     shmemx_desc_t desc[kStageDescs];    // per phase as many as the work-group has wavefronts
 };
+static_assert(alignof(PlanStage) == 16 && offsetof(PlanStage, desc) % 16 == 0, "descriptors are staged in 16-byte vectors");
 
 // `staged`: the task's descriptors in LDS, or null.
 __device__ __forceinline__ void run_task(const shmemx_dctx_pub_t &c, const shmemx_desc_t *D, const PlanTask &t,
