@@ -1109,8 +1109,8 @@ __host__ __device__ __forceinline__ uint64_t udiv(uint64_t x, uint64_t d)
 }
 
 // How a multicast of Q source ranges of n bytes to P members is cut into
-// tasks: chunks of a range (all of one size, whole 4 KiB pages of the
-// destination's lines where they are long) times groups of members.  With
+// tasks: chunks of a range (all of one size, no larger than `chunk`, a
+// multiple of 4 KiB where they are long) times groups of members.  With
 // enough ranges and chunks of the launch's size a task writes its chunk to
 // every member, and the chunks shrink until the last round of tasks is full.
 // With less than half a task per worker, chunks are at most 64 KiB (four
@@ -1152,7 +1152,7 @@ __host__ __device__ __forceinline__ McastSplit mcast_split(uint64_t n, uint32_t 
     }
     McastSplit m;
     const uint64_t even = udiv(n + k - 1, k), line = even >= (16u << 10) ? 4096 : 16;
-    m.chunk = (even + line - 1) & ~(line - 1);
+    m.chunk = least((even + line - 1) & ~(line - 1), chunk);
     m.nch = udiv(n + m.chunk - 1, m.chunk);
     m.per = (P + g - 1) / g;
     m.groups = (P + m.per - 1) / m.per;

@@ -455,4 +455,16 @@ int usertest_moves(const void *dctx, int npes, int scope, int get, const uint64_
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// The same for a multicast of Q ranges of n bytes to P members: bytes per
+// chunk, chunks per range, members per task, groups of members.
+int usertest_mcast_split(uint64_t n, uint32_t Q, uint32_t P, uint32_t workers, uint64_t chunk, uint64_t *out)
+{
+    const vshmem_detail::McastSplit m = vshmem_detail::mcast_split(n, Q, P, workers, chunk);
+    out[0] = m.chunk;
+    out[1] = m.nch;
+    out[2] = m.per;
+    out[3] = m.groups;
+    return 0;
+}
+
 }  // extern "C"

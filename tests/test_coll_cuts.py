@@ -44,3 +44,18 @@ def test_blocks_stay_whole_where_units_have_many(lib, n):
         lib.usertest_pair_split(1, ctypes.c_uint64(n), P, workers, wg, ctypes.c_uint64(256 << 10), out)
         parts = -(-n // (256 << 10))
         assert out[1] == parts and out[0] - (n - (parts - 1) * out[0]) < parts * 8192, (P, workers, wg, out[0])
+
+
+@pytest.mark.parametrize("chunk", [16, 4096, 20000, 65536, 100000, 262144])
+def test_multicast_chunks_stay_within_the_callers(lib, chunk):
+    """A chunk is no larger than asked for, chunks cover the range, groups the
+    members, none of them empty."""
+    out = (ctypes.c_uint64 * 4)()
+    for n in (1, 15, 4096, 16384, 20000, 100001, 300000, 1 << 20, 5 << 20, 256 << 20):
+        for P in (1, 4, 13, 64, 500):
+            for Q in (1, P):
+                for workers in (1, P, 4 * P, 256, 1024):
+                    lib.usertest_mcast_split(ctypes.c_uint64(n), Q, P, workers, ctypes.c_uint64(chunk), out)
+                    size, nch, per, groups = out
+                    assert 0 < size <= chunk and (nch - 1) * size < n <= nch * size, (n, P, Q, workers, size)
+                    assert (groups - 1) * per < P <= groups * per, (n, P, Q, workers)
