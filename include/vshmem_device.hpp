@@ -1602,6 +1602,8 @@ struct RedWavesSplit {
     uint64_t tpt, ntask;   // tiles of 64 vectors per task, tasks
     uint32_t m, G;         // member blocks, tiles per step
 };
+// Bytes per member that a work-group takes in one step.
+__host__ __forceinline__ uint64_t red_step_bytes(uint32_t P, uint32_t waves) { return 1024ull * (waves / ((P + 7) / 8)); }
 __host__ __forceinline__ RedWavesSplit red_waves_split(const uint8_t *d0, uint64_t nelem, uint32_t ES, uint32_t P,
                                                        uint32_t waves, uint64_t chunk)
 {

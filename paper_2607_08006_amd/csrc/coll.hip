@@ -277,25 +277,31 @@ int shmemx_reduce_launch(shmem_team_t team, int dtype, int op, void *dest, const
     // of P / 8 load batches in each of the others.  Splitting the members over
     // wavefronts makes it one batch.  64 members: 8192 vectors of fp32 11.3 ->
     // 5.6 us, of bf16 15.6 -> 6.4; 40960 of fp32 20.0 -> 16.5; 65536 23.0 ->
-    // 24.6; 57 members 49152 19.2 -> 20.2, so up to five eighths of the lanes.
+    // 24.6; 57 members 49152 19.2 -> 20.2, so up to ten sixteenths of the lanes.
     // 40 members (three of eight wavefronts idle): 32768 11.3 -> 8.7, 49152
-    // 12.7 -> 14.8, so half.  24 and 29 members, two tiles per step: 8192 6.3 ->
-    // 5.8, 24576 6.0 -> 5.75, 32768 6.0 -> 6.6, so three eighths.  17 members:
-    // 8192 4.7 and 4.7, bf16 at 16384 5.5 -> 5.8; 13 members 3.8 -> 5.7: not
-    // split.
-    const int eighths = P > 56 ? 5 : P >= 32 ? 4 : P >= 24 ? 3 : 0;
+    // 12.7 -> 14.8; 32 members (two tiles per step) 32768 7.7 -> 6.5, 36864 9.0
+    // -> 10.3: half.  24 and 28 members, two tiles per step: 28672 6.5 -> 5.3 and
+    // 7.4 -> 5.8 (int64 7.6 -> 5.7), 36864 7.1 -> 8.4 and 8.6 -> 9.6 (int64 from
+    // 32768 on), so seven.  17 members: 8192 4.7 and 4.7, bf16 at 16384 5.5 -> 5.8;
+    // 13 members 3.8 -> 5.7: not split.
+    const int sixteenths = P > 56 ? 10 : P >= 32 ? 8 : P >= 24 ? 7 : 0;
     const int split_cu = (bf ? kWavesReduceSplitBf16 : kWavesReduceSplit) * 64 / 512;
     if (!waves && !two && (!launch || (launch->wgs_per_pe == 0 && launch->wg_size == 0 && launch->chunk_bytes == 0)) &&
-        eighths && P <= 64 && 8 * nvec <= eighths * free_cus() * 256 && split_cu * free_cus() >= P) {
+        sixteenths && P <= 64 && 16 * nvec <= sixteenths * free_cus() * 256 && split_cu * free_cus() >= P) {
         waves = true;
         L.wg_size = 512;
-        g.chunk = 1024;   // one tile of 64 vectors
+        // One tile of 64 vectors per work-group while every tile has one, then
+        // what a step of the work-group's wavefronts takes (24 members, fp32,
+        // 16384 vectors: 6.0 us with one of two tile slots idle, 4.9 so; 1024
+        // vectors of 32 members, int64, 5.3 in steps of two, 4.6 in one).
+        g.chunk = nvec <= 64 * (free_cus() / P * P) ? 1024 : vshmem_detail::red_step_bytes((uint32_t)P, 8);
     }
     // Work-groups: two per CU, while each still has 128 vectors (64 members,
     // fp32, 2^20 elements: 91.6 us with two per CU, 94.5 with one; 2^22
     // elements 358 and 355, so above 2048 vectors per CU one); split over
     // wavefronts, one per tile step.
-    const int64_t per_step = waves ? 64 * std::max<int64_t>(1, 8 / ((P + 7) / 8)) : 128;
+    const int64_t step_vecs = 64 * std::max<int64_t>(1, 8 / ((P + 7) / 8));
+    const int64_t per_step = waves ? std::max<int64_t>(64, std::min<int64_t>(g.chunk / 16, step_vecs)) : 128;
     const int64_t aw = std::min<int64_t>((nvec <= 2048 * free_cus() ? 2 : 1) * free_cus(), (nvec + per_step * P - 1) / (per_step * P) * P);
     const bool nt = (L.flags & SHMEMX_LAUNCH_NONTEMPORAL) != 0;
     const int per_cu = waves ? (bf ? kWavesReduceSplitBf16 : kWavesReduceSplit)

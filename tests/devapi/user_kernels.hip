@@ -467,4 +467,16 @@ int usertest_mcast_split(uint64_t n, uint32_t Q, uint32_t P, uint32_t workers, u
     return 0;
 }
 
+// The same for a reduction over `waves` wavefronts whose task is one step:
+// tiles per task, tiles per step, member blocks.
+int usertest_red_waves_split(uint64_t nelem, uint32_t es, uint32_t P, uint32_t waves, uint64_t *out)
+{
+    const vshmem_detail::RedWavesSplit m = vshmem_detail::red_waves_split(
+        nullptr, nelem, es, P, waves, vshmem_detail::red_step_bytes(P, waves));
+    out[0] = m.tpt;
+    out[1] = m.G;
+    out[2] = m.m;
+    return 0;
+}
+
 }  // extern "C"

@@ -59,3 +59,14 @@ def test_multicast_chunks_stay_within_the_callers(lib, chunk):
                     size, nch, per, groups = out
                     assert 0 < size <= chunk and (nch - 1) * size < n <= nch * size, (n, P, Q, workers, size)
                     assert (groups - 1) * per < P <= groups * per, (n, P, Q, workers)
+
+
+@pytest.mark.parametrize("P", [8, 9, 17, 24, 25, 31, 32, 33, 40, 64])
+def test_a_reduction_step_leaves_no_tile_slot_idle(lib, P):
+    """A task of one step holds as many tiles as the work-group's wavefronts
+    take at a time, members in blocks of eight."""
+    out = (ctypes.c_uint64 * 3)()
+    for waves in range((P + 7) // 8, 9):
+        lib.usertest_red_waves_split(ctypes.c_uint64(100000), 4, P, waves, out)
+        tpt, slots, blocks = out
+        assert blocks == (P + 7) // 8 and slots == waves // blocks and tpt == slots, (waves, list(out))
