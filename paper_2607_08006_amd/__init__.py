@@ -69,11 +69,14 @@ def _torch():
 def _stream(stream) -> int:
     if stream is None:
         t = _torch()
-        if not t.cuda.is_initialized():
+        raw = getattr(t._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(t._C, "_cuda_getDevice", None)
+        if raw is None or device is None or not t.cuda.is_initialized():
             return t.cuda.current_stream().cuda_stream
         # The same handle without a Stream object around it: 0.4 us instead of
-        # 2.9, of the 6.2 us that a small collective's call took.
-        return t._C._cuda_getCurrentRawStream(t._C._cuda_getDevice())
+        # 2.9, of the 6.2 us that a small collective's call took.  (Functions of
+        # torch's own, not of its interface.)
+        return raw(device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
