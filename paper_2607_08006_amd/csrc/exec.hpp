@@ -209,7 +209,14 @@ __device__ __forceinline__ void exec_wg(const shmemx_dctx_pub_t &c, const shmemx
 // barrier; NONE before the first, whose arrival finds it.  Every work-group's
 // stores are written back before its arrival (one release for all of its
 // wavefronts, which have waited for their own), and every work-group
-// invalidates after the wait.
+// invalidates after the wait.  The number is published without a release of
+// its own, which would write the L2 back a second time: everything it stands
+// for was in memory before the arrivals that it was counted from, the
+// publisher's own stores with them, and nothing is stored in between.  (The
+// language's memory model would want the release; the hardware's caches do
+// not: a write-back has completed when the arrival's add is performed.)  A
+// work-group that gives up a wait still arrives at every later barrier, so a
+// launch that timed out leaves a whole number of barriers in the count.
 constexpr uint64_t kNoBarrierYet = ~0ull;
 __device__ __forceinline__ void phase_barrier(const shmemx_dctx_pub_t &c, uint64_t *bar, uint32_t units, uint64_t &g)
 {
