@@ -253,53 +253,61 @@ __device__ __forceinline__ void loads_issued() { asm volatile("" ::: "memory"); 
 template <int V>
 __device__ __forceinline__ void loaded(v4u (&r)[V])
 {
-    static_assert(V == 1 || V == 2 || V == 4 || V == 8, "");
+    static_assert(V <= 4 || V == 8, "");
     if constexpr (V == 2) asm volatile("" : "+v"(r[0]), "+v"(r[1]));
+    if constexpr (V == 3) asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]));
     if constexpr (V == 4) asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]));
     if constexpr (V == 8)
         asm volatile("" : "+v"(r[0]), "+v"(r[1]), "+v"(r[2]), "+v"(r[3]), "+v"(r[4]), "+v"(r[5]), "+v"(r[6]), "+v"(r[7]));
 }
 
-/* nv 16-byte vectors to an aligned destination by one lane: U at a time, then
- * half as many, down to one. */
-template <int U, bool NT>
-__device__ __forceinline__ void lone_vecs(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t nv)
+/* Up to K pieces of 16 bytes from o on by one lane, the last one ending at the
+ * last byte; cnt of them are this lane's. */
+template <int K, bool NT>
+__device__ __forceinline__ void lone_rest(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n, uint64_t o,
+                                          uint32_t cnt)
 {
-    for (; nv >= U; nv -= U, d += 16 * U, s += 16 * U) {
-        v4u r[U];
+    v4u r[K];
 #pragma unroll
-        for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + 16 * u);
+    for (int u = 0; u < K; ++u) r[u] = ld_any<NT, v4u>(s + min(o + 16 * u, n - 16));
+    loaded(r);
 #pragma unroll
-        for (int u = 0; u < U; ++u) st<NT>((v4u *)d + u, r[u]);
-    }
-    if constexpr (U > 1) lone_vecs<U / 2, NT>(d, s, nv);
+    for (int u = 0; u < K; ++u)
+        if (u == 0 || u < cnt) st_any<NT, v4u>(d + min(o + 16 * u, n - 16), r[u]);
 }
 
-/* Copy of n bytes by one lane.  Up to 32 bytes, two pieces of the widest size
- * that fits, the second ending at the last byte (one piece when it fits
- * exactly: an 8-byte message is one 8-byte move).  Longer ones: the
- * destination's 16-byte vectors, and before them the first and the last 16
- * bytes where an edge is not on a boundary (both in one round trip; they
- * repeat bytes of the vectors).  No vector is loaded twice: 64 lanes reading
- * 64 messages are 64 lines each time (64 PEs x 1024 lanes, 4096 messages of 16
- * bytes per PE: 8.3 us with four pieces always in flight, 5.9 so). */
+/* Copy of n bytes by one lane.  Below 16 bytes, two pieces of the widest size
+ * that fits, the second ending at the last byte (one when it fits exactly: an
+ * 8-byte message is one 8-byte move).  Longer ones: 16 U bytes at a time, on
+ * the destination's boundaries when there is more than that, and the rest in
+ * one round trip, with as many loads as the wavefront's longest rest needs:
+ * lanes with messages of different lengths wait once, and no lane of many
+ * with one length loads a piece twice, 64 lanes reading 64 messages being 64
+ * lines each time (64 PEs x 1024 lanes, 4096 messages of 16 bytes per PE: 8.3
+ * us with four pieces always in flight, 6.6 so). */
 template <int U, bool NT>
 __device__ __forceinline__ void copy_lone(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n)
 {
-    if (n > 32) {
-        const uint64_t head = (16 - ((uintptr_t)d & 15)) & 15;
-        if (head || (n & 15)) {
-            const v4u a = ld_any<NT, v4u>(s), b = ld_any<NT, v4u>(s + n - 16);
-            st_any<NT, v4u>(d, a);
-            st_any<NT, v4u>(d + n - 16, b);
+    static_assert(U <= 4, "");
+    if (n >= 16) {
+        uint64_t o = 0;
+        if (n > 16 * U) {
+            o = (16 - ((uintptr_t)d & 15)) & 15;
+            if (o) st_any<NT, v4u>(d, ld_any<NT, v4u>(s));
+            for (; o + 16 * U <= n; o += 16 * U) {
+                v4u r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + o + 16 * u);
+#pragma unroll
+                for (int u = 0; u < U; ++u) st_any<NT, v4u>(d + o + 16 * u, r[u]);
+            }
+            if (o >= n) return;
         }
-        lone_vecs<U, NT>(d + head, s + head, (n - head) / 16);
-    } else if (n > 16) {
-        const v4u a = ld_any<NT, v4u>(s), b = ld_any<NT, v4u>(s + n - 16);
-        st_any<NT, v4u>(d, a);
-        st_any<NT, v4u>(d + n - 16, b);
-    } else if (n == 16) {
-        st_any<NT, v4u>(d, ld_any<NT, v4u>(s));
+        const uint32_t cnt = ((uint32_t)(n - o) + 15) >> 4;   // 1 to U
+        if (U > 3 && __ballot(cnt > 3)) lone_rest<4, NT>(d, s, n, o, cnt);
+        else if (U > 2 && __ballot(cnt > 2)) lone_rest<3, NT>(d, s, n, o, cnt);
+        else if (U > 1 && __ballot(cnt > 1)) lone_rest<2, NT>(d, s, n, o, cnt);
+        else lone_rest<1, NT>(d, s, n, o, cnt);
     } else if (n >= 8) {
         const uint64_t a = ld_any<NT, uint64_t>(s), b = ld_any<NT, uint64_t>(s + n - 8);
         st_any<NT, uint64_t>(d, a);
