@@ -289,70 +289,81 @@ template <int U, bool NT>
 __device__ __forceinline__ void copy_lone(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n)
 {
     static_assert(U <= 4, "");
-    if (n >= 16) {
-        uint64_t o = 0;
-        if (n > 16 * U) {
-            o = (16 - ((uintptr_t)d & 15)) & 15;
-            if (o) st_any<NT, v4u>(d, ld_any<NT, v4u>(s));
-            for (; o + 16 * U <= n; o += 16 * U) {
-                v4u r[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + o + 16 * u);
-#pragma unroll
-                for (int u = 0; u < U; ++u) st_any<NT, v4u>(d + o + 16 * u, r[u]);
-            }
-            if (o >= n) return;
+    if (n < 16) {
+        if (n >= 8) {
+            const uint64_t a = ld_any<NT, uint64_t>(s), b = ld_any<NT, uint64_t>(s + n - 8);
+            st_any<NT, uint64_t>(d, a);
+            if (n > 8) st_any<NT, uint64_t>(d + n - 8, b);
+        } else if (n >= 4) {
+            const uint32_t a = ld_any<NT, uint32_t>(s), b = ld_any<NT, uint32_t>(s + n - 4);
+            st_any<NT, uint32_t>(d, a);
+            if (n > 4) st_any<NT, uint32_t>(d + n - 4, b);
+        } else if (n >= 2) {
+            const uint16_t a = ld_any<NT, uint16_t>(s), b = ld_any<NT, uint16_t>(s + n - 2);
+            st_any<NT, uint16_t>(d, a);
+            if (n > 2) st_any<NT, uint16_t>(d + n - 2, b);
+        } else if (n) {
+            *d = *s;
         }
-        const uint32_t cnt = ((uint32_t)(n - o) + 15) >> 4;   // 1 to U
-        if (U > 3 && __ballot(cnt > 3)) lone_rest<4, NT>(d, s, n, o, cnt);
-        else if (U > 2 && __ballot(cnt > 2)) lone_rest<3, NT>(d, s, n, o, cnt);
-        else if (U > 1 && __ballot(cnt > 1)) lone_rest<2, NT>(d, s, n, o, cnt);
-        else lone_rest<1, NT>(d, s, n, o, cnt);
-    } else if (n >= 8) {
-        const uint64_t a = ld_any<NT, uint64_t>(s), b = ld_any<NT, uint64_t>(s + n - 8);
-        st_any<NT, uint64_t>(d, a);
-        if (n > 8) st_any<NT, uint64_t>(d + n - 8, b);
-    } else if (n >= 4) {
-        const uint32_t a = ld_any<NT, uint32_t>(s), b = ld_any<NT, uint32_t>(s + n - 4);
-        st_any<NT, uint32_t>(d, a);
-        if (n > 4) st_any<NT, uint32_t>(d + n - 4, b);
-    } else if (n >= 2) {
-        const uint16_t a = ld_any<NT, uint16_t>(s), b = ld_any<NT, uint16_t>(s + n - 2);
-        st_any<NT, uint16_t>(d, a);
-        if (n > 2) st_any<NT, uint16_t>(d + n - 2, b);
-    } else if (n) {
-        *d = *s;
+        return;
     }
+    uint64_t o = 0;
+    if (n > 16 * U) {
+        o = (16 - ((uintptr_t)d & 15)) & 15;
+        if (o) st_any<NT, v4u>(d, ld_any<NT, v4u>(s));
+        for (; o + 16 * U <= n; o += 16 * U) {
+            v4u r[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) r[u] = ld_any<NT, v4u>(s + o + 16 * u);
+#pragma unroll
+            for (int u = 0; u < U; ++u) st_any<NT, v4u>(d + o + 16 * u, r[u]);
+        }
+        if (o >= n) return;
+    }
+    const uint32_t cnt = ((uint32_t)(n - o) + 15) >> 4;   // 1 to U
+    if (U > 3 && __ballot(cnt > 3)) lone_rest<4, NT>(d, s, n, o, cnt);
+    else if (U > 2 && __ballot(cnt > 2)) lone_rest<3, NT>(d, s, n, o, cnt);
+    else if (U > 1 && __ballot(cnt > 1)) lone_rest<2, NT>(d, s, n, o, cnt);
+    else lone_rest<1, NT>(d, s, n, o, cnt);
 }
 
 /* Pieces 0 .. np - 1 of 16 bytes by nl lanes, V in flight per lane (of whole
  * wavefronts: each takes one contiguous run): piece k at 16 k, at most at
  * `last` (which may lie before 0), and piece np - 1 at `end`.  np is at most
- * V nl, and one more with MORE, which lane 0 takes.  Lanes past the end load
- * a piece again and no load is under a condition of its own: after a
- * conditional load the compiler puts a wait, a round trip for each. */
-template <int V, bool NT, bool MORE>
+ * V nl; with MORE it may be one more, which lane 0 takes; with LOOP any number.
+ * Lanes past the end load a piece again and no load is under a condition of
+ * its own: after a conditional load the compiler puts a wait, a round trip for
+ * each. */
+enum { FIT, MORE, LOOP };
+template <int V, bool NT, int KIND>
 __device__ __forceinline__ void copy_pieces(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t np,
                                             int64_t last, int64_t end, uint64_t lane, uint64_t nl)
 {
     const bool waves = (nl & 63) == 0;
-    const uint64_t w = waves ? 64 : nl, k = waves ? (lane >> 6) * (V * 64) + (lane & 63) : lane;
+    const uint64_t w = waves ? 64 : nl;
+    uint64_t k = waves ? (lane >> 6) * (V * 64) + (lane & 63) : lane;
     if (k >= np) return;
-    int64_t o[V];
-    v4u r[V], x;
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
+    auto at = [&](int v) {
         const uint64_t q = k + v * w;
-        o[v] = q + 1 >= np ? end : min((int64_t)(16 * q), last);
-        r[v] = ld_any<NT, v4u>(s + o[v]);
-    }
-    const bool more = MORE && np > V * nl;
-    if (more) x = ld_any<NT, v4u>(s + end);
-    loaded(r);
+        return q + 1 >= np ? end : min((int64_t)(16 * q), last);
+    };
+    do {
+        // (The places are computed where they are used: for the stores anew, and
+        // not ahead of a loop over messages.  Kept, they take four registers each.)
+        asm volatile("" : "+v"(k));
+        v4u r[V], x;
 #pragma unroll
-    for (int v = 0; v < V; ++v)
-        if (v == 0 || k + v * w < np) st_any<NT, v4u>(d + o[v], r[v]);
-    if (more && lane == 0) st_any<NT, v4u>(d + end, x);
+        for (int v = 0; v < V; ++v) r[v] = ld_any<NT, v4u>(s + at(v));
+        const bool more = KIND == MORE && np > V * nl;
+        if (more) x = ld_any<NT, v4u>(s + end);
+        loaded(r);
+        asm volatile("" : "+v"(k));
+#pragma unroll
+        for (int v = 0; v < V; ++v)
+            if (v == 0 || k + v * w < np) st_any<NT, v4u>(d + at(v), r[v]);
+        if (more && lane == 0) st_any<NT, v4u>(d + end, x);
+        k += V * nl;
+    } while (KIND == LOOP && k < np);
 }
 
 /* Copy n bytes with nl cooperating lanes (this one is `lane`), at any
@@ -360,7 +371,11 @@ __device__ __forceinline__ void copy_pieces(uint8_t *__restrict__ d, const uint8
  * lie inside the message (stores stay aligned, loads take the source as it
  * falls), and the first and the last 16 bytes where the destination's edges
  * are not on a boundary; those overlap the vectors beside them and write the
- * same bytes.  LONE marks a copy by one lane (lane 0 of 1).
+ * same bytes.  LONE marks a copy by one lane (lane 0 of 1).  R is the number of
+ * pieces a lane keeps in flight in the remainder, U or less.  Without SHORT a
+ * short message takes the longer ones' way: the batches' executors, which run
+ * a few messages of all lengths each, are better off with less code (2000
+ * operations on 64 PEs with completion stamps: 29 us so, 32 with both ways).
  *
  * Bound by HBM for large messages, by a round trip and the instructions around
  * it for short ones: so one piece per lane where the lanes suffice, whatever
@@ -374,7 +389,7 @@ __device__ __forceinline__ void copy_pieces(uint8_t *__restrict__ d, const uint8
  * 6.1 TB/s, against 5.7 with every nl-th vector instead of contiguous runs per
  * wavefront.  What is left behind aligned vectors joined by funnel shifts:
  * sources off a boundary, 16 and 32 KiB by 1024 threads, 247 us and 217. */
-template <int U, bool NT, bool LONE = false>
+template <int U, bool NT, bool LONE = false, int R = U, bool SHORT = true>
 __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_t *__restrict__ s, uint64_t n,
                                            uint64_t lane, uint64_t nl)
 {
@@ -389,7 +404,7 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
     // The destination's vectors that hold bytes of the message, moved inward
     // to lie inside it: one piece per lane where the lanes suffice.
     const uint64_t mis = (uintptr_t)d & 15, np = (mis + n + 15) >> 4;
-    if (np <= nl) {
+    if (SHORT && np <= nl) {
         if (lane < np) {
             const uint64_t o = min(lane ? 16 * lane - mis : 0, n - 16);
             st_any<NT, v4u>(d + o, ld_any<NT, v4u>(s + o));
@@ -404,7 +419,8 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
     // threads moved at 5.6 TB/s, and at 4.6 with every nl-th vector.
     const bool waves = (nl & 63) == 0;
     const uint64_t w = waves ? 64 : nl;
-    const uint64_t first = waves ? (lane >> 6) * (U * 64) + (lane & 63) : lane;
+    uint64_t first = waves ? (lane >> 6) * (U * 64) + (lane & 63) : lane;
+    if (R == U) asm volatile("" : "+v"(first));   // (as in copy_pieces; k_pairs 92 registers without, 76 with)
     v4u *dv = (v4u *)(d + head);
     const uint8_t *sv = s + head;
     uint64_t nb = 0;
@@ -416,7 +432,7 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
 #pragma unroll
         for (int u = 0; u < U; ++u) st<NT>(dv + i + u * w, r[u]);
     }
-    // The rest, in one round trip: the vectors past the batches, the last 16
+    // The rest, in one round trip (R = U): the vectors past the batches, the last 16
     // bytes if the end is off a boundary, and as the last piece the first 16
     // bytes if the start is.
     const uint64_t rest = np - nb;
@@ -425,10 +441,10 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
     const int64_t last = (int64_t)(n - 16 - at), end = head ? -(int64_t)at : last;
     d += at;
     s += at;
-    if (U > 1 && rest <= nl) copy_pieces<1, NT, false>(d, s, rest, last, end, lane, nl);
-    else if (U > 2 && rest <= 2 * nl) copy_pieces<2, NT, false>(d, s, rest, last, end, lane, nl);
-    else if (U > 4 && rest <= 4 * nl) copy_pieces<4, NT, false>(d, s, rest, last, end, lane, nl);
-    else copy_pieces<U, NT, true>(d, s, rest, last, end, lane, nl);
+    if (SHORT && U > 1 && rest <= nl) copy_pieces<1, NT, FIT>(d, s, rest, last, end, lane, nl);
+    else if (SHORT && U > 2 && rest <= 2 * nl) copy_pieces<2, NT, FIT>(d, s, rest, last, end, lane, nl);
+    else if (R > 4 && rest <= 4 * nl) copy_pieces<4, NT, FIT>(d, s, rest, last, end, lane, nl);
+    else copy_pieces<R, NT, R == U ? MORE : LOOP>(d, s, rest, last, end, lane, nl);
 }
 
 __device__ __forceinline__ bool cmp_holds_u(uint64_t x, int cmp, uint64_t v)

@@ -111,12 +111,12 @@ __global__ void __launch_bounds__(MAXT) k_rma_pattern(shmemx_dctx_pub_t c, const
         const uint64_t batch = 16ull * U * nl;
         const bool batches = vshmem_detail::udiv(msg, batch) * batch == msg && (((uintptr_t)D | dstep) & 15) == 0;
         if (sstep == msg && dstep == msg && !batches)
-            vshmem_detail::copy_bytes<U, NT>(D + m0 * msg, S + m0 * msg, (m1 - m0) * msg, lane, nl);
+            vshmem_detail::copy_bytes<U, NT, false, 4>(D + m0 * msg, S + m0 * msg, (m1 - m0) * msg, lane, nl);
         else if (msg >= 16 && !batches && msg < min<uint64_t>(8 * batch, 1u << 30))
             copy_run<vshmem_detail::v4u, 4, NT>(D, S, msg, sstep, dstep, m0, m1, lane, nl);
         else if (msg >= 16)
             for (uint64_t j = unit; j < nmsg; j += units)
-                vshmem_detail::copy_bytes<U, NT>(D + j * dstep, S + j * sstep, msg, lane, nl);
+                vshmem_detail::copy_bytes<U, NT, false, 4>(D + j * dstep, S + j * sstep, msg, lane, nl);
         else if (msg >= 8)
             copy_run<uint64_t, 4, NT>(D, S, msg, sstep, dstep, m0, m1, lane, nl);
         else
