@@ -442,7 +442,7 @@ __device__ __forceinline__ void copy_bytes(uint8_t *__restrict__ d, const uint8_
     d += at;
     s += at;
     if (SHORT && U > 1 && rest <= nl) copy_pieces<1, NT, FIT>(d, s, rest, last, end, lane, nl);
-    else if (SHORT && U > 2 && rest <= 2 * nl) copy_pieces<2, NT, FIT>(d, s, rest, last, end, lane, nl);
+    else if (SHORT && U > 2 && R <= 4 && rest <= 2 * nl) copy_pieces<2, NT, FIT>(d, s, rest, last, end, lane, nl);
     else if (R > 4 && rest <= 4 * nl) copy_pieces<4, NT, FIT>(d, s, rest, last, end, lane, nl);
     else copy_pieces<R, NT, R == U ? MORE : LOOP>(d, s, rest, last, end, lane, nl);
 }
