@@ -153,6 +153,8 @@ def build_rows(v, torch, L: Layout, npes: int, want):
     add("put_grid_64MiB_perm", f, b, kernel="k_rma_pattern<3,true,true,8,256>")
     f, b = rma(v.OP_PUT, v.SCOPE_WAVE, perm, 4096, 4, 256, flags=v.LAUNCH_NONTEMPORAL)
     add("put_wave_4KiB_perm", f, b, kernel="k_rma_pattern<1,true,true,4,256>")
+    # Thread scope: the pattern deals these messages to wavefronts, whose lanes
+    # share them, so the rows measure runs of messages and not one per lane.
     f, b = rma(v.OP_GET, v.SCOPE_THREAD, ring, 64, 4, 256)
     add("get_thread_64B_ring", f, b)
     f, b = rma(v.OP_PUT, v.SCOPE_THREAD, perm, 8, 2, 1024)
@@ -1118,7 +1120,7 @@ def main():
         "vs_baseline": None, "dtype": "u8", "data": "synthetic",
         "config": {"workload": f"{npes} virtual PEs x {args.heap_mib} MiB symmetric heap each (slices "
                                f"{heap_stride // MiB} MiB apart); one pass of every "
-                               "hot-path row (put/get at thread (8 B, 64 B), wavefront (4 KiB), work-group "
+                               "hot-path row (put/get at thread (8 B, 64 B; runs of messages per wavefront), wavefront (4 KiB), work-group "
                                "(16 MiB) and grid (64 MiB) scope on ring and derangement patterns, 2^26 random "
                                "fetch_xor/fetch_add on a 2^27-entry int64 table, signal ping-pong 32 pairs x 200, "
                                "100 barriers, broadcast 256 MiB, fcollect 4 MiB, alltoall 1 MiB blocks, sum/max "

@@ -1053,7 +1053,8 @@ __device__ __forceinline__ uint64_t member_stride(const shmem_dctx_t &ctx, const
 // small work-groups and tasks, where the loop's sixteen conditions do (64
 // members, chunks of 8 KiB by 512 threads 78.6 us, 51.8 so; of 4 KiB by 64
 // threads 306 and 139): with 64 members per task and four vectors in each of
-// 1024 lanes the loop is the faster one (16 MiB 178 us against 182).
+// 1024 lanes the loop is the faster one (16 MiB 178 us against 182), with two
+// as well (32 KiB from each of 64 work-groups 40 us this way, 34 through it).
 template <bool NT, int T>
 __device__ __forceinline__ void mcast_small(uint8_t *d0, uint64_t pstride, int P, const uint8_t *s, uint32_t n,
                                             uint32_t worker)

@@ -23,8 +23,9 @@ __device__ __forceinline__ uint64_t splitmix_at(uint64_t seed, uint64_t i)
 // add) while the table fits the 256 MB cache and 19 G/s on 1 GiB, from one
 // wavefront per SIMD on.  Atomics on one word take 12 ns each, so `acc` gets
 // one per work-group: with one per wavefront of 4096 work-groups of 256, up to
-// 200 us of a call were theirs (2^20 updates: 205 us, now 49.5; 2^24 on 2^27
-// words: 949 us, now 893).
+// 200 us of a call were theirs (2^20 updates: 205 us, now 49.5; 2^18 58.7, now
+// 17.1).  2^24 updates on 2^27 words take 800 to 900 us from box to box, all of
+// it the lines', and did before.
 template <bool STORE>
 __global__ void __launch_bounds__(1024) k_gups(shmemx_dctx_pub_t c, uint64_t table_off, uint64_t gmask,
                                               int log2_per_pe, uint64_t nupd, uint64_t seed, uint64_t add_every,

@@ -112,7 +112,8 @@ __device__ __forceinline__ void run_task(const shmemx_dctx_pub_t &c, const shmem
 // trips to memory behind every barrier.  4-PE program of 8 epochs of 125
 // put/get and 10^4 fetch_add: 42.9 us without, 39.8 with the tasks staged and
 // the barrier of phase_barrier, 34.8 with its atomics sorted by word and
-// combined (exec_lanes), too.
+// combined (exec_lanes), too, and 30.2 with copies whose loads wait once
+// (copy_bytes).
 __global__ void __launch_bounds__(1024) k_plan_fused(shmemx_dctx_pub_t c, const shmemx_desc_t *__restrict__ D,
                                                      const PlanTask *__restrict__ T, const uint32_t *__restrict__ phase,
                                                      int nphases, uint64_t *results, uint64_t *stamps, uint64_t *bar)

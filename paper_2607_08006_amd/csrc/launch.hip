@@ -70,7 +70,7 @@ struct Ctl {
 
 // Sections of a workspace for tables of up to `cap` descriptors.  The
 // barrier words come first: count at 0 and generation VSHMEM_SYNC_GEN_OFF
-// further, the layout counter_barrier expects.
+// further, the layout phase_barrier expects.
 struct Ws {
     uint64_t *bar;
     Ctl *ctl;
@@ -843,10 +843,10 @@ __device__ __forceinline__ void index_serial(const BatchArgs &a, SerialLds &L)
 // The serial form is bound by one work-group's latency, 3 ns per descriptor,
 // this one by its chain of dependent steps.  4-PE mixed program (11044
 // descriptors): 36.0 us serial; 12.2 us here and 4.7 us in the scatter kernel,
-// and the whole launch 79.0 -> 58.2 us.  Launches of 300, 16000 and 60000 small
+// and the whole launch 79.0 -> 58.2 us (56.0 with less code in its copies).  Launches of 300, 16000 and 60000 small
 // puts with 64 barriers between 4 PEs: 82.9 -> 62.6, 155 -> 99, 241 -> 106 us.
 // The dearest points are fences of PEs that seldom issue one (each operation
-// searches far back): 4000 puts, 1000 fences, 64 PEs take 183 us, 179 before.
+// searches far back): 4000 puts, 1000 fences, 64 PEs take 183 us, and 181 in the serial form.
 struct ParLds {
     uint64_t cnt[kParBuckets];          // operations << 32 | work-group tasks, of this tile; then before it
     __align__(16) uint32_t point[kParSync];   // table position << 13 | barrier << 12 | issuer; read four at a time
