@@ -1143,7 +1143,7 @@ __host__ __device__ __forceinline__ uint64_t udiv(uint64_t x, uint64_t d)
 // chunks down to 16 KiB (one vector per lane): re-reading a chunk for each
 // group of members costs little, most of the traffic being the writes, and
 // an idle CU costs its share.  One 1024-thread work-group per CU, 64 members:
-// a broadcast of 1 MiB took 137 us as four tasks of 256 KiB and takes 17;
+// a broadcast of 1 MiB took 137 us as four tasks of 256 KiB and takes 15;
 // fcollect of 300000 bytes 258 us in two rounds, the second a quarter full,
 // and 248 in one.  13 members, 256 MiB: chunks of even size but off the line
 // boundaries 1099 us, on them 759.

@@ -841,12 +841,13 @@ __device__ __forceinline__ void index_serial(const BatchArgs &a, SerialLds &L)
 // offsets; k_batch_scatter then writes the sorted order.
 //
 // The serial form is bound by one work-group's latency, 3 ns per descriptor,
-// this one by its chain of dependent steps.  4-PE mixed program (11044
-// descriptors): 36.0 us serial; 12.2 us here and 4.7 us in the scatter kernel,
-// and the whole launch 79.0 -> 58.2 us (56.0 with less code in its copies).  Launches of 300, 16000 and 60000 small
-// puts with 64 barriers between 4 PEs: 82.9 -> 62.6, 155 -> 99, 241 -> 106 us.
+// this one by its chain of dependent steps.  4-PE mixed program (11040
+// descriptors): 36.0 us serial; 13.5 us here and 3.8 us in the scatter kernel,
+// and the whole launch 79.0 -> 58.2 us (55.8 with less code in its copies).
+// Launches of 300, 16000 and 60000 small puts with 64 barriers between 4 PEs:
+// 88.0 -> 66.4, 152 -> 92, 242 -> 100 us.
 // The dearest points are fences of PEs that seldom issue one (each operation
-// searches far back): 4000 puts, 1000 fences, 64 PEs take 183 us, and 181 in the serial form.
+// searches far back): 4000 puts, 1000 fences, 64 PEs take 182 us in either form.
 struct ParLds {
     uint64_t cnt[kParBuckets];          // operations << 32 | work-group tasks, of this tile; then before it
     __align__(16) uint32_t point[kParSync];   // table position << 13 | barrier << 12 | issuer; read four at a time
@@ -1064,7 +1065,7 @@ __global__ void __launch_bounds__(kIndexThreads) k_batch_index(BatchArgs a)
 // Scatter kernel: the sorted order from the parallel index's keys, ranks and
 // offsets, one descriptor per thread.  The order inside a bucket is free: its
 // operations run concurrently anyway.  Two dependent loads and a store: launch
-// latency bounds it (4.7 us for 11044 descriptors).
+// latency bounds it (3.8 us for 11040 descriptors).
 __global__ void __launch_bounds__(256) k_batch_scatter(BatchArgs a)
 {
     const Ws &w = a.w;
@@ -1105,7 +1106,7 @@ __device__ __forceinline__ uint32_t wave_search(const uint64_t *cs, uint32_t lo,
 // Phase bounds, and of the first phases (up to kStageDescs descriptors) the
 // work-group's first task where that is a wavefront pack, are therefore read
 // once, before the first phase.  4-PE mixed program: this kernel took 51.6 us
-// and takes 40.3.
+// and takes 37.8.
 __global__ void __launch_bounds__(1024) k_batch_exec(BatchArgs a)
 {
     __shared__ shmemx_tune_t tune;
